@@ -27,6 +27,7 @@
 // slot of the per-query window also position >= t - W + 1.
 #include <algorithm>
 #include <climits>
+#include <cstring>
 
 #include "block_select.h"
 #include "launch.h"
@@ -43,6 +44,24 @@ constexpr int kMaxCand = 8192;
 // otherwise the 4 waves of a workgroup share one unit (and slice) and split
 // its fragments.
 constexpr int kWpgCand = 4096;
+// How a WPG launch deals its units to waves.  Two waves on a SIMD take as long
+// as one after the other (the tile's MFMA and epilogue issue bound both), so a
+// launch lasts as long as the SIMD with the most work: kSimds units a round,
+// and a last round holding a few units costs as much as a full one.  Units
+// [0, n_full), whole rounds, go one to a wave; each unit past them is cut into
+// `split` candidate slices, one to a wave, so the last round is shared by all
+// SIMDs.  first[b] = units of the sequences before b of the launch (only the
+// groups on the proxy path count, so a ragged batch leaves no empty waves).
+// Measured against one whole unit per wave: the Refine call of 4097 bf16
+// queries after 20000 keys (2050 units) 755 -> 690 us, five packed fp8 requests
+// of 888-3553 queries (2200 units) 984 -> 862 us; 2048 and 7168 units, whole
+// rounds, unchanged.
+struct UnitPlan {
+  int32_t n_units, n_full, split;
+  int32_t first[kMaxSeq + 1];
+};
+constexpr int kSimds = 1024;  // 256 CUs x 4
+
 // Staged positions run kPosPad entries past a wave's (WPG) or workgroup's
 // candidates, holding key 0, so the fetch three fragments ahead (at most
 // 5 fragment strides past the loop's last fragment) reads a position without
@@ -57,7 +76,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     const uint8_t* __restrict__ q, const float* __restrict__ q_scale, const float* __restrict__ w,
     const uint8_t* __restrict__ lin, const float* __restrict__ lin_scale, int g,
     const uint8_t* __restrict__ k, const float* __restrict__ k_scale, KeyMap km, SeqTable st, int j0,
-    const int32_t* __restrict__ cand, int c, int all_slots, int parts, void* __restrict__ rsc) {
+    const int32_t* __restrict__ cand, int c, int all_slots, int zparts, UnitPlan up, void* __restrict__ rsc) {
   using Tile = RowTile<DT, R>;
   constexpr uint32_t SE = OB16 ? 2 : 4;  // bytes per stored score
   constexpr int EB = Tile::EB;
@@ -65,15 +84,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
   __shared__ int32_t spos_all[WPG ? 4 * (kWpgCand + kPosPadWpg) : kMaxCand + kPosPad];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
-  // members [R blk, R blk + R); candidate fragments of slice `part`
-  // WPG: workgroups are dealt round-robin to the 8 XCDs; XCD x % 8 takes a
-  // contiguous run of groups (consecutive groups share most candidates, so
-  // their gathers hit that XCD's L2); a partial last round keeps its order
-  const int nwg = (int)gridDim.x, full = nwg - nwg % 8, bx = (int)blockIdx.x;
-  const int wgx = WPG && bx < full ? (bx % 8) * (full / 8) + bx / 8 : bx;
-  const int nblk = (g + R - 1) / R, unit = 4 * wgx + wave;
-  const int j = j0 + (WPG ? unit / nblk : (int)blockIdx.x), b = blockIdx.y;
-  const int blk = WPG ? unit % nblk : (int)blockIdx.z / parts, part = WPG ? 0 : (int)blockIdx.z % parts;
+  // members [R blk, R blk + R); candidate fragments of slice `part` of `parts`
+  const int nblk = (g + R - 1) / R, bx = (int)blockIdx.x;
+  int b, j, blk, part, parts;
+  if constexpr (WPG) {
+    // workgroups are dealt round-robin to the 8 XCDs; XCD x % 8 takes a
+    // contiguous run of the whole units (consecutive groups share most
+    // candidates, so their gathers hit that XCD's L2)
+    const int nfw = up.n_full / 4;
+    int unit;
+    if (bx < nfw) {
+      unit = 4 * ((bx % 8) * (nfw / 8) + bx / 8) + wave;
+      part = 0;
+      parts = 1;
+    } else {
+      const int sw = 4 * (bx - nfw) + wave;
+      unit = up.n_full + sw / up.split;
+      part = sw % up.split;
+      parts = up.split;
+    }
+    if (unit >= up.n_units) return;  // no workgroup barrier in a WPG launch
+    int hi = st.n;                   // the sequence b with first[b] <= unit < first[b + 1]
+    b = 0;
+    while (hi - b > 1) {
+      const int mid = (b + hi) / 2;
+      if (up.first[mid] <= unit) b = mid;
+      else hi = mid;
+    }
+    const int local = unit - up.first[b];
+    j = max(j0, st.first_proxy[b]) + local / nblk;
+    blk = local % nblk;
+  } else {
+    j = j0 + bx;
+    b = blockIdx.y;
+    blk = (int)blockIdx.z / zparts;
+    part = (int)blockIdx.z % zparts;
+    parts = zparts;
+  }
   if (b >= st.n || j >= seq_groups(st, b, g) || j < st.first_proxy[b]) return;
   const int gs = min(g, st.n_rows[b] - j * g);
   if (R * blk >= gs) return;
@@ -964,6 +1011,43 @@ hipError_t launch_short(const E* rescore, const int32_t* cand, int g, const SeqT
   return hipGetLastError();
 }
 
+// The units of a WPG launch (UnitPlan).  The units past the last whole round
+// are cut into the number of slices with the shortest round time
+//   ceil(rem split / kSimds) (1 / split + kLoadFrags / nfrag),
+// in units of a whole row block: a slice pays the tile load again, which costs
+// about as much as scoring four fragments (four slices to every unit of 256
+// fragments made a 2048-unit launch 4% longer).  Slices keep at least 8
+// fragments.  Where no cut helps, every unit stays whole.
+static UnitPlan plan_units(const SeqTable& st, int g, int R, int j0, int j1, int nfrag) {
+  constexpr double kLoadFrags = 4.0;
+  UnitPlan up;
+  memset(&up, 0, sizeof up);
+  const int nblk = (g + R - 1) / R;
+  int64_t n = 0;
+  for (int b = 0; b < st.n; ++b) {
+    const int ng = (int)(((int64_t)st.n_rows[b] + g - 1) / g);
+    const int lo = std::max(j0, st.first_proxy[b]), hi = std::min(j1, ng);
+    up.first[b] = (int32_t)n;
+    n += (int64_t)std::max(0, hi - lo) * nblk;
+  }
+  for (int b = st.n; b <= kMaxSeq; ++b) up.first[b] = (int32_t)n;
+  up.n_units = (int32_t)n;
+  const int64_t rem = n % kSimds;
+  int best = 1;
+  double cost = 1.0 + kLoadFrags / nfrag;
+  for (int k = 2; k <= std::min(32, nfrag / 8); ++k) {
+    const double t = (double)((rem * k + kSimds - 1) / kSimds) * (1.0 / k + kLoadFrags / nfrag);
+    if (t < cost) {
+      cost = t;
+      best = k;
+    }
+  }
+  up.split = best;
+  // whole units: full rounds, or (nothing cut) the largest multiple of 8 workgroups
+  up.n_full = (int32_t)(best > 1 ? n - rem : n - n % 32);
+  return up;
+}
+
 hipError_t launch_refine(int dtype, const void* q, const float* q_scale, const float* w, const uint8_t* lin,
                          const float* lin_scale, int g, const void* k, const float* k_scale, const KeyMap& km,
                          const SeqTable& st, int j0, int j1, const int32_t* cand, int c, int W, int wslot, int m,
@@ -1001,8 +1085,12 @@ hipError_t launch_refine(int dtype, const void* q, const float* q_scale, const f
   const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(1, nfrag / 24), (512 + wgs - 1) / wgs));
   // many groups (prefill): one unit per wave when the candidate rows fit its LDS share
   const bool wpg = parts == 1 && c <= kWpgCand;
-  const int64_t units = (int64_t)(j1 - j0) * ((g + R - 1) / R);
-  const dim3 grid = wpg ? dim3((unsigned)((units + 3) / 4), (unsigned)st.n, 1u)
+  UnitPlan up;
+  memset(&up, 0, sizeof up);
+  if (wpg) up = plan_units(st, g, R, j0, j1, nfrag);
+  const int64_t waves = up.n_full + (int64_t)(up.n_units - up.n_full) * up.split;
+  if (wpg && waves == 0) return hipSuccess;
+  const dim3 grid = wpg ? dim3((unsigned)((waves + 3) / 4))
                         : dim3((unsigned)(j1 - j0), (unsigned)st.n, (unsigned)(((g + R - 1) / R) * parts));
   // 32-bit gather offsets when every gatherable key row lies below 2^31 bytes
   // (a paged pool always does)
@@ -1011,11 +1099,11 @@ hipError_t launch_refine(int dtype, const void* q, const float* q_scale, const f
 #define PIVOT_RESCORE(DTV, RV, OB, WP, KS)                                                                        \
   if (b32)                                                                                                        \
     hipLaunchKernelGGL((rescore_kernel<DTV, RV, OB, WP, true>), grid, dim3(256), 0, stream, (const uint8_t*)q,     \
-                       q_scale, w, lin, lin_scale, g, (const uint8_t*)k, KS, km, st, j0, cand, c, all_slots, parts, \
+                       q_scale, w, lin, lin_scale, g, (const uint8_t*)k, KS, km, st, j0, cand, c, all_slots, parts, up, \
                        rescore);                                                                                  \
   else                                                                                                            \
     hipLaunchKernelGGL((rescore_kernel<DTV, RV, OB, WP, false>), grid, dim3(256), 0, stream, (const uint8_t*)q,    \
-                       q_scale, w, lin, lin_scale, g, (const uint8_t*)k, KS, km, st, j0, cand, c, all_slots, parts, \
+                       q_scale, w, lin, lin_scale, g, (const uint8_t*)k, KS, km, st, j0, cand, c, all_slots, parts, up, \
                        rescore)
   if (dtype == kFp8 && R == 4) {
     if (wpg) PIVOT_RESCORE(kFp8, 4, true, true, k_scale);

@@ -1,0 +1,70 @@
+"""How launches deal their work: sizes at which the last round of a Refine
+launch holds a few row blocks only, so that they are cut into candidate slices
+and shared by all SIMDs, and batches whose sequences hold different numbers of
+groups on the proxy path."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2607_24593_amd as pv
+from gpu_util import dev, host, say
+from parity import check_pivot
+from workload.gen import make_prefill
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def inputs():
+    return {f: make_prefill(7400, f, seed=81, threads=8) for f in ("fp8", "bf16")}
+
+
+# fp8 blocks hold 4 members, bf16 blocks 2: groups of 4 make 1 or 2 blocks a group
+@pytest.mark.parametrize("fmt,p0,n_q,g,c,topk", [
+    ("fp8", 2100, 4 * 1024, 4, 1024, 300),       # 1024 blocks: one whole round, none cut
+    ("fp8", 2100, 4 * 1024 + 1, 4, 1024, 300),   # one block of one member past it
+    ("fp8", 2100, 4 * 1300 - 3, 4, 2040, 300),   # a quarter of a round past it, ragged candidate tail
+    ("fp8", 2100, 5001, 8, 1000, 300),           # two blocks a group, ragged last group of one
+    ("fp8", 2100, 2 * 600, 2, 1024, 300),        # less than a round (2-row blocks), all cut
+    ("bf16", 2100, 2 * 1100 + 1, 2, 1016, 300),  # 1101 blocks
+    ("bf16", 2100, 4 * 513, 4, 1024, 300),       # 1026 blocks of two a group
+])
+def test_refine_tail_blocks(inputs, fmt, p0, n_q, g, c, topk):
+    """Sampled groups, the last ones (the cut blocks) among them, against the oracle."""
+    x, n_k, ng = inputs[fmt], p0 + n_q, -(-n_q // g)
+    say("refine tail", fmt, n_q, g, c)
+    qs = None if x.q_scale is None else x.q_scale[p0:n_k]
+    ks = None if x.k_scale is None else x.k_scale[:n_k]
+    cand = torch.full((1, ng, c), -7, dtype=torch.int32, device="cuda")
+    idx = pv.pivot_group_index(dev(x.q[p0:n_k]), dev(qs), dev(x.w[p0:n_k]), dev(x.k[:n_k]), dev(ks), p0, n_k, topk,
+                               mode=pv.PIVOT_REFINE, g=g, c=c, out_cand=cand)
+    rng = np.random.default_rng(3)
+    groups = sorted({0, 1, ng - 3, ng - 2, ng - 1} | set(int(v) for v in rng.integers(0, ng, 8)))
+    check_pivot(fmt, x.q[p0:n_k], qs, x.w[p0:n_k], p0, x.k[:n_k], ks, n_k, mode=oracle.REFINE, g=g, c=c, topk=topk,
+                dense_below=-1, gpu_idx=host(idx), gpu_cand=host(cand)[0], groups=groups, label="tail")
+
+
+def test_refine_ragged_batch_matches_single_calls(inputs):
+    """Packed runs with different numbers of proxy groups (one sequence wholly
+    on the guardrail, one empty, one of a single query) give each sequence the
+    sets of its own call."""
+    x, g, c, topk = inputs["fp8"], 4, 1024, 300
+    runs = [(0, 900), (1500, 2303), (3000, 0), (5000, 1), (2000, 2401)]  # (first position, queries)
+    cu = np.concatenate([[0], np.cumsum([n for _, n in runs])])
+    rows = np.concatenate([np.arange(p, p + n) for p, n in runs])
+    lens = [p + max(n, 1) for p, n in runs]
+    k = torch.zeros(len(runs), max(lens), 128, dtype=torch.uint8, device="cuda")
+    ks = torch.ones(len(runs), max(lens), device="cuda")
+    for b, n in enumerate(lens):
+        k[b, :n], ks[b, :n] = dev(x.k[:n]), dev(x.k_scale[:n])
+    say("refine ragged batch", runs)
+    got = host(pv.pivot_group_index_layout(dev(x.q[rows]), dev(x.q_scale[rows]), dev(x.w[rows]), k, ks,
+                                           [p for p, _ in runs], lens, topk, pv.make_layout(cu), pv.PIVOT_REFINE, g, c))
+    for b, (p, n) in enumerate(runs):
+        if n == 0:
+            continue
+        e = p + n
+        one = host(pv.pivot_group_index(dev(x.q[p:e]), dev(x.q_scale[p:e]), dev(x.w[p:e]), dev(x.k[:e]),
+                                        dev(x.k_scale[:e]), p, e, topk, mode=pv.PIVOT_REFINE, g=g, c=c))
+        assert np.array_equal(np.sort(got[cu[b]:cu[b + 1]], 1), np.sort(one, 1)), (b, p, n)
