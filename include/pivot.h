@@ -350,8 +350,8 @@ pivot_status pivot_topk_rows_bf16(int32_t n_rows, const uint16_t* scores, int64_
 /*
  * Stage: pivot_topk_rows with a device workspace (256-B aligned, or NULL).
  * With at least pivot_topk_rows_workspace_size(n_rows) bytes, a call of at
- * most 256 rows whose longest row has >= 16384 entries splits every row over
- * several workgroups (the decode shape of the index paths); otherwise it
+ * most 256 rows whose longest row has more than 65536 entries (or at least
+ * 16384 when m > 4608) splits every row over several workgroups; otherwise it
  * runs as pivot_topk_rows.  The result is the same either way.
  * pivot_topk_rows_workspace_size returns 0 for n_rows outside [1, 256].
  */

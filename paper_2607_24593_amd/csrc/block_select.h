@@ -66,35 +66,46 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
   return x;
 }
 
-// Find the digit d (of `bins`) where the running count crosses `rem`, scanning
-// digits downwards (desc) or upwards (!desc).  Threads take the digits in scan
-// order, bins/THREADS consecutive ones each (one, or none, when bins is
-// smaller): with DESC thread 0 holds the highest digits, so one ascending
-// scan over the lanes and waves serves both directions.  Writes sh.digit,
-// sh.before (count strictly before d in scan order) and sh.equal (count at
-// d).  Contains workgroup barriers.
-template <int THREADS, bool DESC>
-__device__ __forceinline__ void find_digit(const uint32_t* hist, SelectShared& sh, uint32_t rem, int bins) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int per = bins / THREADS;  // bins is a multiple of THREADS, or smaller
-  const int cnt = per > 0 ? per : (tid < bins ? 1 : 0);
-  const int first = per > 0 ? (DESC ? bins - 1 - per * tid : per * tid) : (DESC ? bins - 1 - tid : tid);
-  auto digit = [&](int k) { return DESC ? first - k : first + k; };  // k-th digit of this thread in scan order
-  uint32_t tot = 0;
-  for (int k = 0; k < cnt; ++k) tot += hist[digit(k)];
+// Find the digit d (of BINS) where the running count crosses `rem`, scanning
+// digits downwards (DESC) or upwards.  Threads take the digits in scan order,
+// BINS / THREADS consecutive ones each (one, or none, when BINS is smaller):
+// with DESC thread 0 holds the highest digits, so one ascending scan over the
+// lanes and waves serves both directions.  Writes sh.digit, sh.before (count
+// strictly before d in scan order) and sh.equal (count at d).  Contains
+// workgroup barriers.  A serial chain of LDS reads bounds it, so a thread
+// keeps its counts in registers and the waves' totals are read by 16 lanes at
+// once and scanned there (a loop over them cost up to 15 round trips).
+template <int THREADS, bool DESC, int BINS>
+__device__ __forceinline__ void find_digit(const uint32_t* hist, SelectShared& sh, uint32_t rem) {
+  static_assert(BINS % THREADS == 0 || BINS < THREADS, "bins per thread");
+  static_assert(THREADS <= 1024, "the waves' totals fit one row of 16 lanes");
+  constexpr int PER = BINS >= THREADS ? BINS / THREADS : 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool active = BINS >= THREADS || tid < BINS;
+  const int first = DESC ? BINS - 1 - PER * tid : PER * tid;
+  uint32_t h[PER], tot = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) h[k] = active ? hist[DESC ? first - k : first + k] : 0u;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) tot += h[k];
   const uint32_t s = wave_incl_sum(tot);
   if (lane == 63) sh.wsum[wv] = s;
   __syncthreads();
-  uint32_t before = s - tot;
-  for (int w = 0; w < wv; ++w) before += sh.wsum[w];
-  for (int k = 0; k < cnt; ++k) {
-    const uint32_t h = hist[digit(k)];
-    if (before < rem && rem <= before + h) {
-      sh.digit = digit(k);
+  uint32_t x = (lane & 15) < THREADS / 64 ? sh.wsum[lane & 15] : 0u;
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);  // row_shr:1, 2, 4, 8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
+  uint32_t before = s - tot + (wv > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)x, wv > 0 ? wv - 1 : 0) : 0u);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (before < rem && rem <= before + h[k]) {
+      sh.digit = DESC ? first - k : first + k;
       sh.before = before;
-      sh.equal = h;
+      sh.equal = h[k];
     }
-    before += h;
+    before += h[k];
   }
   __syncthreads();
 }
@@ -146,7 +157,7 @@ __device__ void block_select(const Src& src, uint32_t need, SelectShared& sh, Pu
     __syncthreads();
     src.visit([&](uint32_t key, int32_t) { atomicAdd(&sh.hist[bucket(key)], 1u); });
     __syncthreads();
-    find_digit<THREADS, true>(sh.hist, sh, rem, 256);
+    find_digit<THREADS, true, 256>(sh.hist, sh, rem);
     bsel = (int)sh.digit;
     rem -= sh.before;
     equal = sh.equal;
@@ -175,7 +186,7 @@ __device__ void block_select(const Src& src, uint32_t need, SelectShared& sh, Pu
       if ((key & fixed) == prefix && member(key)) atomicAdd(&sh.hist[(key >> shift) & dmask], 1u);
     });
     __syncthreads();
-    find_digit<THREADS, true>(sh.hist, sh, rem, 256);
+    find_digit<THREADS, true, 256>(sh.hist, sh, rem);
     rem -= sh.before;
     equal = sh.equal;
     prefix |= sh.digit << shift;
@@ -195,7 +206,7 @@ __device__ void block_select(const Src& src, uint32_t need, SelectShared& sh, Pu
         if (key == T && (p & imask) == ipref) atomicAdd(&sh.hist[(p >> shift) & 255u], 1u);
       });
       __syncthreads();
-      find_digit<THREADS, false>(sh.hist, sh, rem, 256);
+      find_digit<THREADS, false, 256>(sh.hist, sh, rem);
       rem -= sh.before;
       ipref |= sh.digit << shift;
       imask |= 255u << shift;
@@ -306,7 +317,7 @@ __device__ bool bucket_select(const Src& src, uint32_t need, uint32_t* hist, uin
   __syncthreads();
   src.visit([&](uint32_t key, int32_t) { atomicAdd(&hist[bucket(key)], 1u); });
   __syncthreads();
-  find_digit<THREADS, true>(hist, sh, need, NB);
+  find_digit<THREADS, true, NB>(hist, sh, need);
   const int bsel = (int)sh.digit;
   const uint32_t rem = need - sh.before, in_b = sh.equal;
   __syncthreads();
@@ -357,7 +368,7 @@ __device__ void two_level_select(const Src& src, uint32_t m, TwoLevelShared<CAP>
   __syncthreads();
   src.visit([&](uint32_t key, int32_t) { atomicAdd(&hist[key >> 20], 1u); });
   __syncthreads();
-  find_digit<THREADS, true>(hist, sh.sel, m, 4096);  // the bin holding the m-th key
+  find_digit<THREADS, true, 4096>(hist, sh.sel, m);  // the bin holding the m-th key
   const uint32_t b1 = sh.sel.digit, above = sh.sel.before, in_b1 = sh.sel.equal;
   __syncthreads();
   if (in_b1 <= (uint32_t)CAP) {

@@ -763,7 +763,7 @@ __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], con
     for (int v = 0; v < V; ++v) atomicAdd(&hist[usable(v) ? bucket(fv(v), fmin, scale) : NB], 1u);
   }
   __syncthreads();
-  find_digit<T, true>(hist, sh, m, NB);
+  find_digit<T, true, NB>(hist, sh, m);
   const int bsel = (int)sh.digit;
   const uint32_t rem = m - sh.before, in_b = sh.equal;
   __syncthreads();  // the histogram's words become the boundary list

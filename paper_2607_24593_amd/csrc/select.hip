@@ -1,8 +1,12 @@
 // Per-row top-m selection over score rows of fp32, or of bf16 (the rows the
 // fp8 path writes; every bf16 value widens exactly to the fp32 it selects
-// on), for the TopK of Sec. 3.1 and of Eqs. 6-7: one 512-thread workgroup per row (1024 threads when a launch
-// holds at most 256 long rows), or, for such a launch given scratch (decode),
-// the split select described below.
+// on), for the TopK of Sec. 3.1 and of Eqs. 6-7, one workgroup per row:
+//   rows of at most 32768 scores (131072 bf16 or 65536 fp32 ones when a launch
+//     has at most 256 rows, as in decode): topk_resident_kernel, the whole row
+//     in registers;
+//   longer rows: 512 threads streaming the row (topk_rows16_kernel for bf16,
+//     topk_rows_kernel), or, for a launch of at most 256 rows given scratch,
+//     the split select described below.
 //
 // Long rows (n >= kSampleMinLen) are read once when the expected number of
 // compacted keys fits in LDS:
@@ -61,6 +65,9 @@ constexpr int kSplitSlots = 2 * kSelCapLarge;
 constexpr int kSplitMinP = 4, kSplitMaxP = 16;
 constexpr int kSplitPerMax = kSplitSlots / kSplitMinP;
 constexpr int kSplitTargetBlocks = 1024;
+// Largest m of the resident select: the sample's threshold then keeps at most
+// 80% of its candidate buffer (kSelCap16) for every row length it takes.
+constexpr int kResidentMaxM = 4608;
 
 // Elements of a score row (fp32 or bf16, E), visited with 16-byte vector
 // loads (U in flight per thread) when aligned.
@@ -124,7 +131,7 @@ __device__ uint32_t sample_prefix(const Src& src, uint32_t ts, uint32_t* hist, S
   __syncthreads();
   src.visit([&](uint32_t key, int32_t) { atomicAdd(&hist[key >> 20], 1u); });
   __syncthreads();
-  find_digit<T, true>(hist, sh, ts, 4096);
+  find_digit<T, true, 4096>(hist, sh, ts);
   const uint32_t d1 = sh.digit, rem = ts - sh.before;
   __syncthreads();
   for (int k = tid; k < 256; k += T) hist[k] = 0;
@@ -133,10 +140,28 @@ __device__ uint32_t sample_prefix(const Src& src, uint32_t ts, uint32_t* hist, S
     if ((key >> 20) == d1) atomicAdd(&hist[(key >> 12) & 255u], 1u);
   });
   __syncthreads();
-  find_digit<T, true>(hist, sh, rem, 256);
+  find_digit<T, true, 256>(hist, sh, rem);
   const uint32_t thr = (d1 << 8) | sh.digit;
   __syncthreads();
   return thr;
+}
+
+// A key near the ts-th largest sampled key (ts <= sampled count), from one
+// pass over the top 12 key bits: the place of the ts-th key inside its bin (an
+// eighth of an octave) is taken in proportion to its rank there.  The tail's
+// density falls by less than half over such a bin, so the count above the
+// result is a few per cent of the bin off, well inside the four standard
+// deviations that ts allows for.
+template <int T, class Src>
+__device__ __forceinline__ uint32_t sample_base(const Src& src, uint32_t ts, uint32_t* hist, SelectShared& sh) {
+  const int tid = threadIdx.x;
+  for (int k = tid; k < 4096; k += T) hist[k] = 0;
+  __syncthreads();
+  src.visit([&](uint32_t key, int32_t) { atomicAdd(&hist[key >> 20], 1u); });
+  __syncthreads();
+  find_digit<T, true, 4096>(hist, sh, ts);
+  const float below = (float)(sh.equal - (ts - sh.before)) / (float)sh.equal;  // in [0, 1)
+  return (sh.digit << 20) + min((uint32_t)(below * 0x1p20f), 0xFFFFFu);
 }
 
 // Steps 1 of the one-read path for a long aligned row: false (before any
@@ -587,6 +612,38 @@ __device__ __forceinline__ int stream_compact16(const bf16_t* row, int n, float 
   return over ? CAP + 1 : tot;
 }
 
+// The `rem` lowest of the in_b positions listed in LDS (members of one value).
+template <int T, class Put>
+__device__ __forceinline__ void take_tied(const int32_t* lpos, uint32_t in_b, uint32_t rem, SelectShared& sh,
+                                          Put put) {
+  const int tid = threadIdx.x;
+  if (in_b <= (uint32_t)kBucketList) {  // rank each tied member by its position, G threads to a member
+    constexpr int G = T / kBucketList;
+    static_assert(G >= 1 && (G & (G - 1)) == 0 && G <= 64, "threads per tied member");
+    const int t = tid / G, part = tid % G;
+    const bool mine = t < (int)in_b;
+    const int32_t p = mine ? lpos[t] : 0;
+    const int span = ((int)in_b + G - 1) / G, u1 = min((int)in_b, (part + 1) * span);
+    uint32_t r = 0;
+    int u = part * span;
+    for (; u + 8 <= u1; u += 8) {
+      int32_t x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = lpos[u + j];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) r += (uint32_t)(x[j] < p);
+    }
+    for (; u < u1; ++u) r += (uint32_t)(lpos[u] < p);
+#pragma unroll
+    for (int o = 1; o < G; o <<= 1) r += __shfl_xor(r, o, 64);
+    wave_append(mine && part == 0 && r < rem, &sh.emitted, [&](int slot) { put(slot, p); });
+    __syncthreads();
+  } else {  // many ties: a radix select on their positions (the keys are equal)
+    const TieSource<T> ties{lpos, (int)in_b};
+    block_select<T, false>(ties, rem, sh, put);
+  }
+}
+
 // Step 3 for bf16 rows, from the histogram the compaction built: b* = the bin
 // holding the m-th largest key; every candidate in a higher bin is taken, and
 // bin b* (below the top bin) holds one bf16 value, so its members tie and the
@@ -597,7 +654,7 @@ template <int T, class Src, class Put>
 __device__ bool select16(const Src& cand, uint32_t base16, uint32_t m, uint32_t* hist, int32_t* lpos,
                          int32_t* lcount, SelectShared& sh, Put put) {
   const int tid = threadIdx.x;
-  find_digit<T, true>(hist, sh, m, kNB16);  // ends with a barrier
+  find_digit<T, true, kNB16>(hist, sh, m);  // ends with a barrier
   const uint32_t bsel = sh.digit, rem = m - sh.before, in_b = sh.equal;
   if (bsel == (uint32_t)(kNB16 - 1) || in_b > (uint32_t)kNB16) return false;
   if (tid == 0) *lcount = 0;
@@ -608,19 +665,7 @@ __device__ bool select16(const Src& cand, uint32_t base16, uint32_t m, uint32_t*
     if (d == bsel) lpos[atomicAdd(lcount, 1)] = p;
   });
   __syncthreads();
-  if (in_b <= (uint32_t)kBucketList) {  // rank each tied member by its position
-    static_assert(T >= kBucketList, "one thread per tied member");
-    const bool mine = tid < (int)in_b;
-    const int32_t p = mine ? lpos[tid] : 0;
-    uint32_t r = 0;
-    if (mine)
-      for (int u = 0; u < (int)in_b; ++u) r += (uint32_t)(lpos[u] < p);
-    wave_append(mine && r < rem, &sh.emitted, [&](int slot) { put(slot, p); });
-    __syncthreads();
-  } else {  // many ties: a radix select on their positions (the keys are equal)
-    const TieSource<T> ties{lpos, (int)in_b};
-    block_select<T, false>(ties, rem, sh, put);
-  }
+  take_tied<T>(lpos, in_b, rem, sh, put);
   return true;
 }
 
@@ -677,6 +722,357 @@ void topk_rows16_kernel(const bf16_t* __restrict__ scores, int64_t ld, SeqTable 
   __syncthreads();  // the region's previous use has ended in every wave
   if (tid == 0) fb.sel.emitted = 0;
   RowSource<T, U, bf16_t> src{row, n};
+  two_level_select<T>(src, (uint32_t)m, fb, put);
+}
+
+// ---- rows held in registers ----
+// Order keys of the resident select: larger score, larger key; -0 and +0 share
+// one; NaNs rank by sign as in float_key; 0 is no score's key.  They are
+// float_key (of a bf16 score its upper half) except that every negative
+// score's key is one higher, which merges the zeros without a compare.  bf16
+// words convert two scores at a time with packed 16-bit operations.
+template <class E>
+struct OrderKey;
+template <>
+struct OrderKey<bf16_t> {
+  static constexpr int kShift = 0;  // histogram bins of one value each
+  typedef short s2 __attribute__((ext_vector_type(2)));
+  __device__ static __forceinline__ uint32_t convert(uint32_t w) {
+    const s2 t = __builtin_bit_cast(s2, w) >> (short)15;
+    const uint32_t k = w ^ (__builtin_bit_cast(uint32_t, t) | 0x80008000u);
+    return __builtin_bit_cast(uint32_t, (s2)(__builtin_bit_cast(s2, k) - t));
+  }
+  __device__ static __forceinline__ uint32_t one(bf16_t h) { return convert(h) & 0xFFFFu; }
+  __device__ static __forceinline__ uint32_t at(const uint4& a, int j) {
+    const uint32_t w = j < 2 ? a.x : j < 4 ? a.y : j < 6 ? a.z : a.w;
+    return (j & 1) ? w >> 16 : w & 0xFFFFu;
+  }
+  // key j >= thr without extracting an upper half
+  __device__ static __forceinline__ bool reaches(const uint4& a, int j, uint32_t thr) {
+    const uint32_t w = j < 2 ? a.x : j < 4 ? a.y : j < 6 ? a.z : a.w;
+    return (j & 1) ? w >= (thr << 16) : (uint16_t)w >= (uint16_t)thr;
+  }
+  __device__ static __forceinline__ bool any_reaches(const uint4& a, uint32_t thr) {
+    typedef unsigned short u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_elementwise_max(__builtin_bit_cast(u2, a.x), __builtin_bit_cast(u2, a.y));
+    const u2 y = __builtin_elementwise_max(__builtin_bit_cast(u2, a.z), __builtin_bit_cast(u2, a.w));
+    const uint32_t k = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(x, y));
+    return max(k >> 16, k & 0xFFFFu) >= thr;
+  }
+  __device__ static __forceinline__ uint32_t wide(uint32_t k) { return k << 16; }
+  __device__ static __forceinline__ uint32_t narrow(uint32_t k) { return k >> 16; }
+  __device__ static __forceinline__ uint32_t as_float_key(uint32_t k) {
+    return (k & 0x8000u) ? k << 16 : ((k - 1u) << 16) | 0xFFFFu;
+  }
+};
+template <>
+struct OrderKey<float> {
+  static constexpr int kShift = 12;  // 1024 bins: half an octave above the threshold
+  __device__ static __forceinline__ uint32_t convert(uint32_t w) {
+    const uint32_t t = (uint32_t)((int32_t)w >> 31);
+    return (w ^ (t | 0x80000000u)) - t;
+  }
+  __device__ static __forceinline__ uint32_t one(float f) { return convert(__float_as_uint(f)); }
+  __device__ static __forceinline__ uint32_t at(const uint4& a, int j) {
+    return j == 0 ? a.x : j == 1 ? a.y : j == 2 ? a.z : a.w;
+  }
+  __device__ static __forceinline__ bool reaches(const uint4& a, int j, uint32_t thr) { return at(a, j) >= thr; }
+  __device__ static __forceinline__ bool any_reaches(const uint4& a, uint32_t thr) {
+    return max(max(a.x, a.y), max(a.z, a.w)) >= thr;
+  }
+  __device__ static __forceinline__ uint32_t wide(uint32_t k) { return k; }
+  __device__ static __forceinline__ uint32_t narrow(uint32_t k) { return k; }
+  __device__ static __forceinline__ uint32_t as_float_key(uint32_t k) { return k - 1u + (k >> 31); }
+};
+
+// One vector of order keys per thread, for sample_prefix.
+template <class E>
+struct ResidentSample {
+  uint4 a;
+  bool ok;
+  template <class F>
+  __device__ __forceinline__ void visit(F f) const {
+    if (ok) {
+#pragma unroll
+      for (int j = 0; j < ScoreVec<E>::N; ++j) f(OrderKey<E>::wide(OrderKey<E>::at(a, j)), 0);
+    }
+  }
+};
+
+// A candidate of the resident select in LDS: one word, the key's distance above
+// the threshold over the position, for bf16 rows of at most 65536 scores, else
+// the key and the position.
+template <class E, bool WORD>
+struct Candidate {
+  using W = uint2;
+  __device__ static __forceinline__ W pack(uint32_t key, uint32_t, int32_t pos) {
+    return make_uint2(key, (uint32_t)pos);
+  }
+  __device__ static __forceinline__ uint32_t above(W w, uint32_t base) { return w.x - base; }
+  __device__ static __forceinline__ int32_t pos(W w) { return (int32_t)w.y; }
+};
+template <>
+struct Candidate<bf16_t, true> {
+  using W = uint32_t;
+  __device__ static __forceinline__ W pack(uint32_t key, uint32_t base, int32_t pos) {
+    return ((key - base) << 16) | (uint32_t)pos;
+  }
+  __device__ static __forceinline__ uint32_t above(W w, uint32_t) { return w >> 16; }
+  __device__ static __forceinline__ int32_t pos(W w) { return (int32_t)(w & 0xFFFFu); }
+};
+
+// The candidates as (float key, position) pairs.
+template <int THREADS, class E, bool WORD>
+struct ResidentCands {
+  using C = Candidate<E, WORD>;
+  const typename C::W* w;
+  uint32_t base;
+  int count;
+  template <class F>
+  __device__ __forceinline__ void visit(F f) const {
+    for (int e = threadIdx.x; e < count; e += THREADS) f(OrderKey<E>::as_float_key(base + C::above(w[e], base)), C::pos(w[e]));
+  }
+};
+
+// Rows of at most T V N scores (N = 8 bf16 or 4 fp32 to a 16-byte vector): one
+// workgroup per row requests all of it at once, V vectors per thread.
+//   1 threshold  wave w's vector w mod vn (vn vectors in use) is the sample,
+//                1/vn of the row in blocks of 64 vectors spread over it
+//                (sample_base).  One vector per thread is the whole row: its
+//                threshold is the m-th key's bin;
+//   2 compact    the keys >= the threshold go to LDS with their positions, a
+//                ballot per score and one LDS atomic per wave and vector;
+//   3 select     a histogram of their distance above the threshold gives the
+//                bin with the m-th key; every candidate above it is taken, and
+//                its members are ranked by (key, position).
+// Outside those rules (the sample's threshold kept fewer than m or more than
+// CAP keys, the m-th key lies past the histogram, the bin is too long) it goes
+// on with bucket_select, block_select or the two-pass select, so every row is
+// exact.
+// FILTER, for few rows (decode), whose threads hold many vectors of which few
+// reach the threshold: step 2 first lists the vectors with a key that does (a
+// packed maximum and one ballot per vector), and examines only those, dealt
+// evenly to the threads and read again (from L2).
+// What bounds it: the fixed phases' latency and LDS operations, not the bytes
+// (a row is a few tens of KiB per CU), so a candidate is one LDS word, and the
+// histogram is built from the candidates rather than score by score; rows of
+// that word leave four 512-thread workgroups to a CU.  Measured against the
+// kernels these rows took before (two passes over the row, a sampled pass, or
+// three launches splitting few long rows): 7168 bf16 rows of 4096-32768 scores
+// 312 -> 150 us, 500 fp32 rows of 20011 (odd stride) 44 -> 20 us, 32 bf16 rows
+// of 131071 32 -> 25 us, 24 of 5003-70001 30 -> 16 us.  Past its limits the
+// row does not fit the registers of one workgroup.
+template <int T, int V, int CAP, class E, bool FILTER>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 && V * (int)sizeof(E) <= 16 ? 8 : 4)))
+void topk_resident_kernel(const E* __restrict__ scores, int64_t ld, SeqTable st, RowSpace rs, OutDesc od) {
+  using OK = OrderKey<E>;
+  constexpr int N = ScoreVec<E>::N;
+  constexpr bool WORD = sizeof(E) == 2 && T * V * N <= 65536;
+  using C = Candidate<E, WORD>;
+  constexpr int CAND_BYTES = ((int)sizeof(typename C::W) * (CAP + 1) + 15) / 16 * 16;  // one slot takes the overflow
+  constexpr int LDS = CAND_BYTES + 4 * kNB16;
+  constexpr int CAP2 = ((LDS - (int)sizeof(TwoLevelShared<0>)) / 8) / 64 * 64;
+  static_assert(CAND_BYTES >= 4 * 4096, "the sampling histogram lies within the candidates");
+  static_assert(CAP2 > 0 && (int)sizeof(TwoLevelShared<CAP2>) <= LDS, "fallback fits the region");
+  __shared__ __attribute__((aligned(16))) uint8_t raw[LDS];
+  __shared__ uint16_t vlist[FILTER ? T * V : 1];  // vectors with a key that reaches the threshold
+  __shared__ SelectShared sel;
+  __shared__ int32_t lcount, kept, listed;
+  const int nrows = rs.i1 - rs.i0;
+  const int b = blockIdx.x / nrows;
+  const int i = rs.i0 + blockIdx.x % nrows;
+  if (!row_active(st, rs, b, i)) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = __builtin_amdgcn_readfirstlane((int)max((int64_t)0, row_limit(st, rs, b, i) + 1));
+  const E* row = scores + ((int64_t)b * nrows + (i - rs.i0)) * ld;
+  const int m = od.m;
+  const RowDest put(od, st, b, i);
+  if (n <= m) {
+    for (int p = tid; p < m; p += T) put(p, p < n ? p : -1);
+    return;
+  }
+  typename C::W* cand = reinterpret_cast<typename C::W*>(raw);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(raw + CAND_BYTES);
+  // the first `head` scores lie before a 16-byte boundary
+  const int head = min(n, (int)((-reinterpret_cast<uintptr_t>(row) & 15u) / sizeof(E)));
+  const int nv = (n - head) / N, vn = (nv + T - 1) / T;  // full vectors, and those of a thread
+  const uint4* r16 = reinterpret_cast<const uint4*>(row + head);
+  if (tid == 0) {
+    sel.emitted = 0;
+    kept = 0;
+    listed = 0;
+  }
+  if (vn >= 1 && vn <= V) {
+    uint4 a[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      a[v] = make_uint4(0u, 0u, 0u, 0u);
+      if (v < vn && v * T + tid < nv) a[v] = r16[v * T + tid];
+    }
+    // the scores before the first vector and after the last: one each for the first threads
+    const int te = tid < head ? tid : tid + N * nv;
+    const uint32_t tkey = te < n && tid < 2 * N ? OK::one(row[te]) : 0u;
+    auto convert = [](uint4 x, bool in) {
+      return make_uint4(in ? OK::convert(x.x) : 0u, in ? OK::convert(x.y) : 0u, in ? OK::convert(x.z) : 0u,
+                        in ? OK::convert(x.w) : 0u);
+    };
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (v < vn) a[v] = convert(a[v], v * T + tid < nv);
+    // lane w: the vector that wave w samples, and the sampled vectors up to it
+    const int turn = lane % vn;
+    const uint32_t sampled =
+        wave_incl_sum(lane < T / 64 ? (uint32_t)max(0, min(64, nv - (turn * T + 64 * lane))) : 0u);
+    const int s = N * __builtin_amdgcn_readlane((int)sampled, 63);
+    const int pick = __builtin_amdgcn_readlane(turn, wave);
+    // expected sample rank of the m-th key plus four standard deviations
+    const float rm = (float)s * (float)m / (float)n;
+    const uint32_t ts = vn == 1 ? (uint32_t)m : (uint32_t)ceilf(rm + 4.0f * sqrtf(rm)) + 1u;
+    const bool all = ts >= (uint32_t)s && n <= CAP;  // nearly every score is wanted: keep them all
+    uint32_t base = 1u;
+    bool ok = all;
+    if (!all && ts < (uint32_t)s && (float)ts * (float)n <= 0.8f * (float)CAP * (float)s) {
+      ResidentSample<E> smp;
+      smp.a = a[0];
+#pragma unroll
+      for (int v = 1; v < V; ++v) {
+        int at = v;  // opaque, or the chain becomes an indexed read of a[] in scratch memory
+        asm volatile("" : "+s"(at));
+        if (at == pick) smp.a = a[v];
+      }
+      smp.ok = pick * T + tid < nv;
+      base = sample_base<T>(smp, ts, reinterpret_cast<uint32_t*>(raw), sel);
+      if (vn == 1) base &= 0xFFF00000u;
+      base = max(OK::narrow(base), 1u);
+      ok = true;
+    }
+    if (ok) {
+      for (int k = tid; k < kNB16; k += T) hist[k] = 0;
+      __syncthreads();  // kept is set, and the sampling histogram's words are free
+      // the keys >= base of vector `x`, whose first position is p0
+      auto compact = [&](const uint4& x, int p0) {
+        uint64_t bal[N];
+        int total = 0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          bal[j] = __ballot(OK::reaches(x, j, base));
+          total += (int)__popcll((unsigned long long)bal[j]);
+        }
+        if (total == 0) return;  // uniform over the wave
+        int slot0 = 0;
+        if (lane == 0) slot0 = atomicAdd(&kept, total);
+        slot0 = __builtin_amdgcn_readfirstlane(slot0);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal[j] >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)bal[j], (uint32_t)slot0));
+          if (OK::reaches(x, j, base)) cand[min(slot, CAP)] = C::pack(OK::at(x, j), base, p0 + j);
+          slot0 += (int)__popcll((unsigned long long)bal[j]);
+        }
+      };
+      if constexpr (FILTER) {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+          if (v < vn) {
+            const bool t = OK::any_reaches(a[v], base);
+            const uint64_t bal = __ballot(t);
+            if (bal == 0) continue;  // uniform over the wave
+            int slot0 = 0;
+            if (lane == 0) slot0 = atomicAdd(&listed, (int)__popcll((unsigned long long)bal));
+            slot0 = __builtin_amdgcn_readfirstlane(slot0);
+            const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)bal, (uint32_t)slot0));
+            if (t) vlist[slot] = (uint16_t)(v * T + tid);
+          }
+        __syncthreads();
+        const int nl = __builtin_amdgcn_readfirstlane(listed);
+        constexpr int U = 4;  // vectors in flight per thread
+        for (int l0 = 0; l0 < nl; l0 += U * T) {
+          uint4 x[U];
+          int q[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int l = l0 + u * T + tid;
+            q[u] = l < nl ? (int)vlist[l] : -1;
+            x[u] = make_uint4(0u, 0u, 0u, 0u);
+            if (q[u] >= 0) x[u] = r16[q[u]];
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (l0 + u * T < nl) compact(convert(x[u], q[u] >= 0), head + N * q[u]);
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+          if (v < vn) compact(a[v], head + N * (v * T + tid));
+      }
+      if (wave == 0)
+        wave_append(tkey >= base, &kept, [&](int slot) { cand[min(slot, CAP)] = C::pack(tkey, base, te); });
+      __syncthreads();
+      const int found = kept;
+      if (found >= m && found <= CAP) {
+        auto bin = [&](typename C::W w) { return min(C::above(w, base) >> OK::kShift, (uint32_t)(kNB16 - 1)); };
+        // the last bin takes every key past the histogram (half of a row whose
+        // threshold is negative): counted by ballot, not by adds to one word
+        int far = 0;
+        for (int e = tid; e < found; e += T) {
+          const uint32_t d = bin(cand[e]);
+          const bool past = d == (uint32_t)(kNB16 - 1);
+          far += (int)__popcll((unsigned long long)__ballot(past));
+          if (!past) atomicAdd(&hist[d], 1u);
+        }
+        if (lane == 0 && far > 0) atomicAdd(&hist[kNB16 - 1], (uint32_t)far);
+        __syncthreads();
+        find_digit<T, true, kNB16>(hist, sel, (uint32_t)m);
+        const uint32_t bsel = sel.digit, rem = (uint32_t)m - sel.before, in_b = sel.equal;
+        constexpr uint32_t kList = sizeof(E) == 2 ? (uint32_t)kNB16 : (uint32_t)kBucketList;
+        if (bsel != (uint32_t)(kNB16 - 1) && in_b <= kList) {
+          uint32_t* lkey = hist;  // free once the bin is known
+          int32_t* lpos = reinterpret_cast<int32_t*>(hist) + (sizeof(E) == 2 ? 0 : kBucketList);
+          if (tid == 0) lcount = 0;
+          __syncthreads();
+          // a wave reserves the slots of all it takes with one atomic
+          int mine = 0;
+          for (int e = tid; e - lane < found; e += T)
+            mine += (int)__popcll((unsigned long long)__ballot(e < found && bin(cand[min(e, CAP)]) > bsel));
+          int slot0 = 0;
+          if (lane == 0) slot0 = atomicAdd(&sel.emitted, mine);
+          slot0 = __builtin_amdgcn_readfirstlane(slot0);
+          for (int e = tid; e - lane < found; e += T) {
+            const typename C::W w = cand[min(e, CAP)];
+            const uint32_t d = bin(w);
+            const bool in = e < found, take = in && d > bsel;
+            const uint64_t bal = __ballot(take);
+            const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)bal, (uint32_t)slot0));
+            if (take) put(slot, C::pos(w));
+            slot0 += (int)__popcll((unsigned long long)bal);
+            if (in && d == bsel) {
+              const int c = atomicAdd(&lcount, 1);
+              if constexpr (sizeof(E) != 2) lkey[c] = base + C::above(w, base);
+              lpos[c] = C::pos(w);
+            }
+          }
+          __syncthreads();
+          if constexpr (sizeof(E) == 2)
+            take_tied<T>(lpos, in_b, rem, sel, put);  // one value: lowest positions
+          else
+            rank_listed<T>(in_b, rem, lkey, lpos, sel, put);
+          return;
+        }
+        const ResidentCands<T, E, WORD> src{cand, base, found};
+        if (!bucket_select<T, kNB16>(src, (uint32_t)m, hist, hist, reinterpret_cast<int32_t*>(hist + kBucketList),
+                                     &lcount, sel, put))
+          block_select<T, false>(src, (uint32_t)m, sel, put);
+        return;
+      }
+    }
+  }
+  TwoLevelShared<CAP2>& fb = *reinterpret_cast<TwoLevelShared<CAP2>*>(raw);
+  __syncthreads();  // the region's previous use has ended in every wave
+  if (tid == 0) fb.sel.emitted = 0;
+  RowSource<T, 4, E> src{row, n};
   two_level_select<T>(src, (uint32_t)m, fb, put);
 }
 
@@ -885,6 +1281,38 @@ static hipError_t topk_launch(const E* scores, int64_t ld, const SeqTable& st, c
   if (nrows <= 0 || st.n <= 0) return hipSuccess;
   const int64_t blocks = (int64_t)st.n * nrows;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  constexpr int N = ScoreVec<E>::N;
+  constexpr int64_t kResident = 32768;  // scores of a 512-thread workgroup's row: 8 (bf16) or 16 (fp32) vectors a thread
+  const int cap_small = od.m <= kSelCapSmall / 2;
+#define PIVOT_RESIDENT(T, V)                                                                                      \
+  do {                                                                                                            \
+    if (cap_small)                                                                                                \
+      hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCapSmall, E, T == kSelThreadsWide>), dim3((unsigned)blocks), dim3(T), 0,       \
+                         stream, scores, ld, st, rs, od);                                                         \
+    else                                                                                                          \
+      hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCap16, E, T == kSelThreadsWide>), dim3((unsigned)blocks), dim3(T), 0, stream,   \
+                         scores, ld, st, rs, od);                                                                 \
+    return hipGetLastError();                                                                                     \
+  } while (0)
+  if (od.m <= kResidentMaxM) {
+    // few rows (decode): a wide workgroup holds up to 131072 bf16 or 65536 fp32 scores
+    if (blocks <= kWideMaxRows && lim_max + 1 <= 16 * kSelThreadsWide * N) PIVOT_RESIDENT(kSelThreadsWide, 16);
+    if (sizeof(E) == 4 && lim_max + 1 <= kResident / 2) PIVOT_RESIDENT(kSelThreads, 8);
+    if (lim_max + 1 <= kResident) PIVOT_RESIDENT(kSelThreads, 32 / N * 2);
+    // one sequence whose rows grow past that: its shorter rows on their own
+    if (st.n == 1 && rs.step > 0) {
+      const int64_t first = (kResident - 1 - st.q_pos0[0]) / rs.step + 1;  // first row longer than kResident
+      if (first - rs.i0 >= kWideMaxRows && first < rs.i1) {
+        RowSpace lo = rs, hi = rs;
+        lo.i1 = hi.i0 = (int32_t)first;
+        const int64_t lim_lo = std::min<int64_t>(lim_max, st.q_pos0[0] + (first - 1) * rs.step);
+        const hipError_t e = topk_launch(scores, ld, st, lo, od, lim_lo, scratch, scratch_bytes, stream);
+        if (e != hipSuccess) return e;
+        return topk_launch(scores + (first - rs.i0) * ld, ld, st, hi, od, lim_max, scratch, scratch_bytes, stream);
+      }
+    }
+  }
+#undef PIVOT_RESIDENT
   if (blocks <= kWideMaxRows && lim_max + 1 >= kSampleMinLen && scratch &&
       scratch_bytes >= split_scratch_bytes(blocks)) {
     // few long rows: P slice workgroups per row, then one merge workgroup
@@ -939,9 +1367,6 @@ static hipError_t topk_launch(const E* scores, int64_t ld, const SeqTable& st, c
   if (small && sample)
     hipLaunchKernelGGL((topk_rows_kernel<kSelCapSmall, kSelThreads, true, E>), grid, block, 0, stream, scores, ld, st, rs,
                        od);
-  else if (small)
-    hipLaunchKernelGGL((topk_rows_kernel<kSelCapSmall, kSelThreads, false, E>), grid, block, 0, stream, scores, ld, st,
-                       rs, od);
   else if (sample)
     hipLaunchKernelGGL((topk_rows_kernel<kSelCapLarge, kSelThreads, true, E>), grid, block, 0, stream, scores, ld, st, rs,
                        od);
