@@ -476,25 +476,34 @@ struct SampleSource16 {
   }
 };
 
-// sample_threshold for bf16 rows with the sample held as packed 16-bit keys,
-// at most SCH chunks: 32 (4096 scores, 1/32 of a 131072-score row) for the
-// large candidate buffer, where the count above the threshold spreads by ~8%
-// of m inside the room CAP leaves; 64 for the small one (m <= 2048), whose
-// room is tighter.  base16 receives the 16-bit key below which no kept key
-// lies.
+// sample_threshold for bf16 rows with the sample held as packed 16-bit keys, in
+// 256-byte chunks: at first SCH of them (32, 4096 scores, for the large
+// candidate buffer, where the count above the threshold spreads by ~8% of m at
+// 131072 scores inside the room CAP leaves; 64 for the small one, m <= 2048,
+// whose room is tighter), doubled up to 128 while the expected count does not
+// fit.  Rows of over 250000 scores need that: with 4096 samples they went to
+// the two-pass select, 950 us a launch of 2040 rows of 245760-262144 instead of 250.
+// base16 receives the 16-bit key below which no kept key lies, fthr its score.
 template <int T, int CAP, int SCH>
 __device__ bool sample_threshold16(const bf16_t* row, int n, int m, uint32_t* hist, SelectShared& sel, float& fthr,
                                    uint32_t& base16) {
-  constexpr int N = 8;
-  constexpr int SV = (SCH * kChunk4 + T - 1) / T;  // sampled 16-byte vectors per thread
+  constexpr int N = 8, MAX = 128;
+  constexpr int SV = MAX * kChunk4 / T;  // sampled 16-byte vectors per thread, at most
   const int tid = threadIdx.x;
   const int nch = n / (N * kChunk4);
-  const int stride = max(16, (nch + SCH - 1) / SCH);
-  const int sch = (nch + stride - 1) / stride;
-  const int s = sch * N * kChunk4;
-  const float rm = (float)s * (float)m / (float)n;
-  const uint32_t ts = (uint32_t)ceilf(rm + 4.0f * sqrtf(rm)) + 1u;
-  if (!(ts < (uint32_t)s && (float)ts * (float)n <= 0.8f * (float)CAP * (float)s)) return false;
+  int stride = 0, sch = 0;
+  uint32_t ts = 0;
+  bool fits = false;
+#pragma unroll 1
+  for (int most = SCH; most <= MAX && !fits; most *= 2) {
+    stride = max(16, (nch + most - 1) / most);
+    sch = (nch + stride - 1) / stride;
+    const int s = sch * N * kChunk4;
+    const float rm = (float)s * (float)m / (float)n;
+    ts = (uint32_t)ceilf(rm + 4.0f * sqrtf(rm)) + 1u;
+    fits = ts < (uint32_t)s && (float)ts * (float)n <= 0.8f * (float)CAP * (float)s;
+  }
+  if (!fits) return false;
   const uint4* r16 = reinterpret_cast<const uint4*>(row);
   SampleSource16<SV> smp;
 #pragma unroll
@@ -507,9 +516,8 @@ __device__ bool sample_threshold16(const bf16_t* row, int n, int m, uint32_t* hi
     smp.pk[4 * v + 2] = key16_pair(a.z);
     smp.pk[4 * v + 3] = key16_pair(a.w);
   }
-  const uint32_t thr = sample_prefix<T>(smp, ts, hist, sel);
-  fthr = key_float(thr << 12);
-  base16 = thr >> 4;
+  base16 = sample_base<T>(smp, ts, hist, sel) >> 16;
+  fthr = key_float(key16_expand(base16));
   return true;
 }
 
