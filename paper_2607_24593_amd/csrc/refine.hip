@@ -747,11 +747,35 @@ __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], con
     }
   }
   uint32_t kmin = float_key(lo), kmax = float_key(hi);
+  // Heavy tails (one score a thousand times the others) would leave the rest
+  // of the row to a bucket or two, whose histogram adds serialise and whose
+  // members overflow the list.  The smallest of the lanes' maxima and the
+  // largest of their minima, of 16 scores each, lie about 1.1 standard
+  // deviations apart whatever the tails do; the range is cut to 4.5 times that
+  // on either side of their middle (beyond every score of a normal row), and
+  // the end buckets take what lies outside.  Lanes with an unusable slot don't
+  // count.  256K keys with Pareto amplitudes, 16384 rows: 222 -> 102 us;
+  // normal rows unchanged.
+  float f_lo = -__builtin_inff(), f_hi = __builtin_inff();
+  if constexpr (V >= 16) {
+    const bool whole = vmask == (uint32_t)((1ull << V) - 1ull);
+    uint32_t inner_hi = whole ? kmax : ~0u, inner_lo = whole ? kmin : 0u;
+    block_pair_reduce<T, true>(inner_hi, inner_lo, sh);  // (min of maxima, max of minima)
+    if (inner_hi != ~0u) {
+      const float a = key_float(inner_lo), c = key_float(inner_hi), reach = 4.5f * fabsf(c - a);
+      f_lo = 0.5f * (a + c) - reach;
+      f_hi = 0.5f * (a + c) + reach;
+    }
+  }
   block_pair_reduce<T, true>(kmin, kmax, sh);
-  const float fmin = key_float(kmin);
-  const float scale = (float)NB / (key_float(kmax) - fmin);
+  // (comparisons that an infinity or NaN fails keep the row's own ends)
+  const float fmin = f_lo > key_float(kmin) ? f_lo : key_float(kmin);
+  const float fmax = f_hi < key_float(kmax) ? f_hi : key_float(kmax);
+  const float scale = (float)NB / (fmax - fmin);
   if (kmin == kmax || !(scale > 0.0f && scale < __builtin_inff())) return false;
-  auto bucket = [&](float f, float f0, float s) { return min(NB - 1, (int)((f - f0) * s)); };
+  auto bucket = [&](float f, float f0, float s) {
+    return (int)__builtin_amdgcn_fmed3f((f - f0) * s, 0.0f, (float)(NB - 1));
+  };
   for (int k = tid; k < NB; k += T) hist[k] = 0;
   if (tid == 0) *lcount = 0;
   __syncthreads();

@@ -68,3 +68,21 @@ def test_refine_ragged_batch_matches_single_calls(inputs):
         one = host(pv.pivot_group_index(dev(x.q[p:e]), dev(x.q_scale[p:e]), dev(x.w[p:e]), dev(x.k[:e]),
                                         dev(x.k_scale[:e]), p, e, topk, mode=pv.PIVOT_REFINE, g=g, c=c))
         assert np.array_equal(np.sort(got[cu[b]:cu[b + 1]], 1), np.sort(one, 1)), (b, p, n)
+
+
+@pytest.mark.parametrize("topk", [1, 200, 2048, 3900, 4095])
+@pytest.mark.parametrize("scale", [1.0, 1e3, 0.0])
+def test_member_select_heavy_tails(topk, scale):
+    """Member rows whose largest scores are far past the others (Pareto keys,
+    some scaled up further; scale 0: a third of the keys are zero, so their
+    scores are equal and lie inside the cut range), selected from 4096 slots:
+    the same sets as the fused path, whose select does not use value ranges."""
+    x = make_prefill(6000, "fp8", seed=83, boost=("pareto", 0.02, 0.7), threads=8)
+    x.k_scale = x.k_scale.copy()
+    x.k_scale[np.arange(6000) % (97 if scale > 0 else 3) == 0] *= np.float32(scale)
+    p0, g, c = 5000, 4, 4096
+    args = (dev(x.q[p0:]), dev(x.q_scale[p0:]), dev(x.w[p0:]), dev(x.k), dev(x.k_scale), p0, 6000, topk)
+    say("heavy tails", topk, scale)
+    a, b = (host(pv.pivot_group_index_opts(*args, mode=pv.PIVOT_REFINE, g=g, c=c, refine_path=path))
+            for path in (pv.PIVOT_REFINE_SPLIT, pv.PIVOT_REFINE_FUSED))
+    assert np.array_equal(np.sort(a, 1), np.sort(b, 1))
