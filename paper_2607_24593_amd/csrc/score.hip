@@ -23,8 +23,10 @@
 // active (row block, segment) pairs still spread evenly over the XCDs
 // (pinning segments to XCDs would idle the XCDs that own the late segments of
 // short prefixes).  Keys mode runs x = key segment, y = sequence.  The segment
-// length adapts to the launch size.
+// length adapts to the launch (score_segment).
+#include <algorithm>
 #include <climits>
+#include <cmath>
 
 #include "launch.h"
 #include "mfma_tile.h"
@@ -297,9 +299,57 @@ __global__ __launch_bounds__(256) void score_kernel(const uint8_t* __restrict__ 
   }
 }
 
-// Workgroups one launch should have for the machine to stay busy through the
-// causal tail: 256 CUs x 2 resident workgroups x 4 rounds.
-constexpr int64_t kTargetWorkgroups = 2048;
+// The key segment of a launch: the power of two in [128, max_seg] with the
+// shortest estimated time.  A workgroup costs its prologue (row tile, scales,
+// first keys: as much as scoring `load` keys) and its keys.
+//   Rows mode (MFMA bound): launches of a few workgroups per CU run in rounds
+// of 256; in long ones the CUs share the sum and end with half a workgroup's
+// time idle: the estimate is the mean of the two.
+//   Keys mode (bound by loads in flight): four workgroups run on a CU at once,
+// each at its own pace, so a round holds 1024.
+// Less than a round takes one workgroup's time.
+// Counted are the (row block, segment) pairs that hold keys.
+//   Measured, us a call (segments of 4096 / 2048 / 1024 / 512 / 256 / 128 keys;
+//   in brackets: the choice):
+//     fp8, five packed requests of 3K-30K keys  795 / [773] / 789 /  -  /  -  /  -
+//     fp8, 8192 queries at 128K, groups of 4  [1780] / 1812 / 1868 /  -  /  -  /  -
+//     fp8, 500 rows of 20K keys                  -  /   -  /   -  /  94 / 113 /  -
+//     bf16, 1025 rows of 24K keys (max 2048)     -  / [667] / 683 /  -  /  -  /  -
+//     bf16, 2048 queries from 0                  -  /   -  /   -  / 101 /  95 /  94
+//     fp8, 24 decode rows of 5K-70K keys         -  / 64 / [50.7] / 55.2 / - / -
+//     bf16, 8 decode rows of 40K keys            -  / 80 /  78 / [78] /  82 /  92
+static int score_segment(const SeqTable& st, const RowSpace& rs, int rb, int max_seg, bool keys_mode,
+                         int load) {
+  double keys[kMaxSeq], blocks[kMaxSeq], all_keys = 0.0;
+  for (int b = 0; b < st.n; ++b) {
+    const int cnt = rs.kind == kProxyRows ? (st.n_rows[b] + rs.step - 1) / rs.step : st.n_rows[b];
+    int hi = std::min(rs.i1, cnt), lo = rs.i0;
+    if (rs.kind == kDenseRows) hi = std::min(hi, st.dense_rows[b]);
+    if (rs.kind == kProxyRows) lo = std::max(lo, st.first_proxy[b]);
+    keys[b] = blocks[b] = 0.0;
+    if (hi <= lo) continue;
+    blocks[b] = (hi - 1 - rs.i0) / rb - (lo - rs.i0) / rb + 1;  // row blocks
+    keys[b] = std::max(0.0, st.q_pos0[b] + 0.5 * ((double)lo + hi - 1) * rs.step + 1.0);  // a block's mean keys
+    all_keys += blocks[b] * keys[b];
+  }
+  int best = max_seg;
+  double best_cost = 0.0;
+  for (int seg = max_seg; seg >= 128; seg >>= 1) {
+    double wgs = 0.0;
+    // a block's segments: of its mean keys (keys mode: a block's rows end together)
+    for (int b = 0; b < st.n; ++b)
+      wgs += blocks[b] * (keys_mode ? std::ceil(keys[b] / seg) : std::max(1.0, keys[b] / seg + 0.5));
+    const double wg = load + seg, slots = keys_mode ? 1024.0 : 256.0;
+    const double rounds = std::ceil(wgs / slots) * wg;
+    const double even = (wgs * load + all_keys) / slots + 0.5 * wg;
+    const double cost = wgs <= slots ? wg : keys_mode ? rounds : 0.5 * (rounds + even);
+    if (seg == max_seg || cost < best_cost) {
+      best = seg;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
 
 template <int DT, int R, bool KSPLIT, bool OB16>
 static hipError_t run_score(const void* q, const float* qs, const float* w, const uint8_t* lin, const float* lsc,
@@ -309,10 +359,8 @@ static hipError_t run_score(const void* q, const float* qs, const float* w, cons
   constexpr int RB = KSPLIT ? R : 4 * R;
   const int nrows = rs.i1 - rs.i0;
   const int64_t nblk = (int64_t)st.n * ((nrows + RB - 1) / RB);
-  // Longest key segment that still gives kTargetWorkgroups (down to 512 keys);
-  // longer segments amortise the row-tile load over more keys.
-  int seg = max_seg;  // <= 4096: the key scales of a segment are staged in LDS
-  while (seg > 512 && nblk * ((lim_max + seg) / seg) < kTargetWorkgroups) seg >>= 1;
+  // <= 4096: the key scales of a segment are staged in LDS
+  const int seg = score_segment(st, rs, RB, max_seg, KSPLIT, !KSPLIT && DT == kBf16 ? 256 : 160);
   const int64_t nseg = (lim_max + seg) / seg;
   if (KSPLIT ? (nseg > 0x7FFFFFFF || nblk > 65535) : nseg * nblk > 0x7FFFFFFF)
     return hipErrorInvalidConfiguration;

@@ -86,3 +86,47 @@ def test_member_select_heavy_tails(topk, scale):
     a, b = (host(pv.pivot_group_index_opts(*args, mode=pv.PIVOT_REFINE, g=g, c=c, refine_path=path))
             for path in (pv.PIVOT_REFINE_SPLIT, pv.PIVOT_REFINE_FUSED))
     assert np.array_equal(np.sort(a, 1), np.sort(b, 1))
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "bf16"])
+@pytest.mark.parametrize("page", [16, 256, 4096])
+@pytest.mark.parametrize("g", [1, 2, 3, 20])
+def test_short_segments_paged_equal_contiguous(inputs, fmt, page, g):
+    """Few short sequences take key segments of 128 or 256 keys, smaller than a
+    page or a whole number of pages; limits fall on, before and after a segment
+    edge.  Paged and contiguous keys give the same sets, and both the sets of a
+    call on each sequence alone (whose segments may differ)."""
+    x, lens, topk = inputs[fmt], [127 + g, 128 + g, 129 + g, 1024, 2049, 7391], 100
+    runs = [(n - g, g) for n in lens]
+    rows = np.concatenate([np.arange(p, p + n) for p, n in runs])
+    cu = np.concatenate([[0], np.cumsum([n for _, n in runs])])
+    need = [-(-n // page) for n in lens]
+    order = np.random.default_rng(page + g).permutation(sum(need)).astype(np.int32)
+    table = np.zeros((len(lens), max(need)), np.int32)
+    pool = np.zeros((sum(need), page, 128), x.k.dtype)
+    pool_s = np.ones((sum(need), page), np.float32)
+    first = 0
+    for b, n in enumerate(lens):
+        mine = order[first:first + need[b]]
+        first += need[b]
+        table[b, :need[b]] = mine
+        whole, sc = np.zeros((need[b] * page, 128), x.k.dtype), np.ones(need[b] * page, np.float32)
+        whole[:n] = x.k[:n]
+        if fmt == "fp8":
+            sc[:n] = x.k_scale[:n]
+        pool[mine], pool_s[mine] = whole.reshape(-1, page, 128), sc.reshape(-1, page)
+    q, w = dev(x.q[rows]), dev(x.w[rows])
+    qs = dev(x.q_scale[rows]) if fmt == "fp8" else None
+    ps = dev(pool_s.reshape(-1)) if fmt == "fp8" else None
+    lay = pv.make_layout(cu, dev(table), page, sum(need) * page)
+    say("short segments", fmt, page, g)
+    args = (q, qs, w, dev(pool.reshape(-1, 128)), ps, [p for p, _ in runs], lens, topk, lay)
+    dense = np.sort(host(pv.pivot_dense_index_layout(*args)), 1)
+    refine = np.sort(host(pv.pivot_group_index_layout(*args, pv.PIVOT_REFINE, g, 2 * topk)), 1)
+    for b, (p, n) in enumerate(runs):
+        e = p + n
+        one = (dev(x.q[p:e]), dev(x.q_scale[p:e]) if fmt == "fp8" else None, dev(x.w[p:e]), dev(x.k[:e]),
+               dev(x.k_scale[:e]) if fmt == "fp8" else None, p, e, topk)
+        assert np.array_equal(dense[cu[b]:cu[b + 1]], np.sort(host(pv.pivot_dense_index(*one)), 1)), b
+        one_r = host(pv.pivot_group_index(*one, mode=pv.PIVOT_REFINE, g=g, c=2 * topk))
+        assert np.array_equal(refine[cu[b]:cu[b + 1]], np.sort(one_r, 1)), b
