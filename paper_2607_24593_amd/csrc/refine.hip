@@ -688,7 +688,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(V <= 16 ? 8 :
       sel.emitted = 0;
     }
     __syncthreads();
-    atomicAdd(&nvalid_sh, mine);
+    {
+      const uint32_t n = wave_incl_sum((uint32_t)mine);  // one add per wave (one per thread: 15 -> 12 us a decode launch)
+      if ((tid & 63) == 63) atomicAdd(&nvalid_sh, (int)n);
+    }
     __syncthreads();
     const int nvalid = nvalid_sh;
     if (nvalid <= m) {  // every usable slot is selected, then -1 padding
@@ -934,7 +937,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void top
       sel.emitted = 0;
     }
     __syncthreads();
-    atomicAdd(&nvalid_sh, __popc(vmask));
+    {
+      const uint32_t n = wave_incl_sum((uint32_t)__popc(vmask));  // one add per wave (one per thread: 90 -> 78 us at 8900 rows)
+      if ((tid & 63) == 63) atomicAdd(&nvalid_sh, (int)n);
+    }
     __syncthreads();
     const int nvalid = nvalid_sh;
     if (nvalid <= m) {  // every usable slot is selected, then -1 padding
@@ -960,30 +966,38 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void top
   block_select<T, true>(src, (uint32_t)m, sel, [&](int slot, int32_t p) { orow[slot] = p; });
 }
 
+constexpr int kWindowThreads = 512;  // with dedupe; without, one wave writes the few slots
+
 // App. B window union: slot0 + u (u < wg) of every candidate row of the
 // groups [j0, j1) with j >= first_proxy[b] takes position t0 - W + 1 + u, or
 // -1 below 0, past the group's last member, or (dedupe) when it is already
 // among the row's first slot0 slots.
-__global__ __launch_bounds__(256) void window_kernel(int32_t* __restrict__ cand, int g, SeqTable st, int j0,
+__global__ __launch_bounds__(kWindowThreads) void window_kernel(int32_t* __restrict__ cand, int g, SeqTable st, int j0,
                                                      int width, int slot0, int W, int wg, int dedupe) {
   __shared__ uint8_t seen[kMaxCand];
   const int j = j0 + blockIdx.x, b = blockIdx.y;
   if (b >= st.n || j >= seq_groups(st, b, g) || j < st.first_proxy[b]) return;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
   const int gs = min(g, st.n_rows[b] - j * g);
   const int64_t t0 = (int64_t)st.q_pos0[b] + (int64_t)j * g;
   const int64_t lo = t0 - W + 1;
   int32_t* row = cand + ((int64_t)st.grp0[b] + j) * width;
   if (dedupe) {
-    for (int u = tid; u < wg; u += 256) seen[u] = 0;
+    for (int u = tid; u < wg; u += kWindowThreads) seen[u] = 0;
     __syncthreads();
-    for (int i = tid; i < slot0; i += 256) {
-      const int64_t p = row[i];
-      if (p >= lo && p < lo + wg) seen[p - lo] = 1;
+    // eight slots per thread in flight: one memory round trip for 4096 slots
+    // (a round trip per slot and thread took 7.3 us of a decode step, this 4.9)
+    for (int i0 = tid; i0 < slot0; i0 += 8 * kWindowThreads) {
+      int64_t p[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) p[k] = i0 + k * kWindowThreads < slot0 ? row[i0 + k * kWindowThreads] : -1;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (p[k] >= 0 && p[k] >= lo && p[k] < lo + wg) seen[p[k] - lo] = 1;
     }
     __syncthreads();
   }
-  for (int u = tid; u < wg; u += 256) {
+  for (int u = tid; u < wg; u += nt) {
     const int64_t p = lo + u;
     const bool ok = p >= 0 && p <= t0 + gs - 1 && !(dedupe && seen[u]);
     row[slot0 + u] = ok ? (int32_t)p : -1;
@@ -995,8 +1009,8 @@ hipError_t launch_window(int32_t* cand, int g, const SeqTable& st, int j0, int j
   const int wg = W + g - 1;
   if (j1 <= j0 || st.n <= 0 || W <= 0) return hipSuccess;
   if (width > kMaxCand || slot0 < 0 || slot0 + wg > width) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(window_kernel, dim3((unsigned)(j1 - j0), (unsigned)st.n), dim3(256), 0, stream, cand, g, st, j0,
-                     width, slot0, W, wg, (int)dedupe);
+  hipLaunchKernelGGL(window_kernel, dim3((unsigned)(j1 - j0), (unsigned)st.n), dim3(dedupe ? kWindowThreads : 64), 0,
+                     stream, cand, g, st, j0, width, slot0, W, wg, (int)dedupe);
   return hipGetLastError();
 }
 
@@ -1017,6 +1031,9 @@ hipError_t launch_short(const E* rescore, const int32_t* cand, int g, const SeqT
     PIVOT_SHORT(4, 256);
   else if (few && c <= 4096 && sizeof(E) == 2)
     hipLaunchKernelGGL((topk_member16_kernel<4, 1024>), sgrid, dim3(1024), 0, stream,
+                       reinterpret_cast<const uint16_t*>(rescore), cand, g, st, j0, nj, c, rule, m, out_idx);
+  else if (few && sizeof(E) == 2)  // c = 4096 plus a window union, or a larger budget
+    hipLaunchKernelGGL((topk_member16_kernel<8, 1024>), sgrid, dim3(1024), 0, stream,
                        reinterpret_cast<const uint16_t*>(rescore), cand, g, st, j0, nj, c, rule, m, out_idx);
   else if (few && c <= 4096)
     PIVOT_SHORT(4, 1024);
