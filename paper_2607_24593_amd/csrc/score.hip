@@ -299,50 +299,79 @@ __global__ __launch_bounds__(256) void score_kernel(const uint8_t* __restrict__ 
   }
 }
 
-// The key segment of a launch: the power of two in [128, max_seg] with the
-// shortest estimated time.  A workgroup costs its prologue (row tile, scales,
-// first keys: as much as scoring `load` keys) and its keys.
+// sum over i in [0, n) of floor((a + b i) / m), a, b >= 0, m > 0.
+static int64_t floor_sum(int64_t n, int64_t m, int64_t b, int64_t a) {
+  int64_t s = 0;
+  while (n > 0) {
+    s += n * (n - 1) / 2 * (b / m) + n * (a / m);
+    b %= m;
+    a %= m;
+    const int64_t top = a + b * n;
+    if (top < m) break;
+    n = top / m;  // the same points counted along the other axis
+    a = top % m;
+    std::swap(m, b);
+  }
+  return s;
+}
+
+// The key segment of a launch: the length with the shortest estimated time, a
+// multiple of 64 keys up to max_seg (paged keys: a power of two of at least 128,
+// so that a segment starts on a page boundary or lies inside one page).  A
+// workgroup costs its prologue (row tile, scales, first keys: as much as scoring
+// `load` keys) and its keys.
 //   Rows mode (MFMA bound): launches of a few workgroups per CU run in rounds
 // of 256; in long ones the CUs share the sum and end with half a workgroup's
 // time idle: the estimate is the mean of the two.
-//   Keys mode (bound by loads in flight): four workgroups run on a CU at once,
-// each at its own pace, so a round holds 1024.
-// Less than a round takes one workgroup's time.
-// Counted are the (row block, segment) pairs that hold keys.
+//   Keys mode (bound by loads in flight): four fp8 or two bf16 workgroups run
+// on a CU at once, each at its own pace, so a round holds 1024 or 512.
+// Less than a round takes one workgroup's time.  Counted are the (row block,
+// segment) pairs that hold keys.
 //   Measured, us a call (segments of 4096 / 2048 / 1024 / 512 / 256 / 128 keys;
-//   in brackets: the choice):
+//   in brackets: the choice among these):
 //     fp8, five packed requests of 3K-30K keys  795 / [773] / 789 /  -  /  -  /  -
 //     fp8, 8192 queries at 128K, groups of 4  [1780] / 1812 / 1868 /  -  /  -  /  -
-//     fp8, 500 rows of 20K keys                  -  /   -  /   -  /  94 / 113 /  -
+//     fp8, 500 rows of 20K keys                  -  /   -  /   -  / [94] / 113 /  -
 //     bf16, 1025 rows of 24K keys (max 2048)     -  / [667] / 683 /  -  /  -  /  -
 //     bf16, 2048 queries from 0                  -  /   -  /   -  / 101 /  95 /  94
 //     fp8, 24 decode rows of 5K-70K keys         -  / 64 / [50.7] / 55.2 / - / -
-//     bf16, 8 decode rows of 40K keys            -  / 80 /  78 / [78] /  82 /  92
-static int score_segment(const SeqTable& st, const RowSpace& rs, int rb, int max_seg, bool keys_mode,
-                         int load) {
-  double keys[kMaxSeq], blocks[kMaxSeq], all_keys = 0.0;
+//     bf16, 8 decode rows of 40K keys            -  / 80 / 74.4 / 72.7 / 76.5 / 92
+//   and at 640 keys [69.5]; 500 rows of 20K keys at 1280 and 2560 keys 90, [91];
+//   fp8, 32 decode rows of 128K keys at 2048, 1536 and 1024 keys [159.6], 163, 164.5
+static int score_segment(const SeqTable& st, const RowSpace& rs, int rb, int max_seg, bool keys_mode, bool fp8,
+                         bool paged) {
+  const int load = keys_mode || fp8 ? 160 : 256;
+  const double slots = !keys_mode ? 256.0 : fp8 ? 1024.0 : 512.0;
+  struct Blocks {
+    int64_t n, first, step;  // row blocks, keys of the first one, keys more per block
+  } seq[kMaxSeq];
+  int64_t all_keys = 0;
   for (int b = 0; b < st.n; ++b) {
     const int cnt = rs.kind == kProxyRows ? (st.n_rows[b] + rs.step - 1) / rs.step : st.n_rows[b];
     int hi = std::min(rs.i1, cnt), lo = rs.i0;
     if (rs.kind == kDenseRows) hi = std::min(hi, st.dense_rows[b]);
     if (rs.kind == kProxyRows) lo = std::max(lo, st.first_proxy[b]);
-    keys[b] = blocks[b] = 0.0;
+    seq[b] = Blocks{0, 0, 0};
     if (hi <= lo) continue;
-    blocks[b] = (hi - 1 - rs.i0) / rb - (lo - rs.i0) / rb + 1;  // row blocks
-    keys[b] = std::max(0.0, st.q_pos0[b] + 0.5 * ((double)lo + hi - 1) * rs.step + 1.0);  // a block's mean keys
-    all_keys += blocks[b] * keys[b];
+    const int64_t b0 = (lo - rs.i0) / rb, b1 = (hi - 1 - rs.i0) / rb;
+    // a block scans the keys of its last row; the last block's last row is hi - 1
+    const int64_t end0 = std::min<int64_t>(rs.i0 + (b0 + 1) * rb, hi) - 1;
+    const int64_t k0 = st.q_pos0[b] + end0 * rs.step + 1, d = (int64_t)rb * rs.step;
+    const int64_t skip = k0 > 0 ? 0 : d > 0 ? (-k0) / d + 1 : b1 - b0 + 1;  // blocks with no key in reach
+    const int64_t n = std::max<int64_t>(0, b1 - b0 + 1 - skip);
+    seq[b] = Blocks{n, k0 + skip * d, d};
+    all_keys += n * seq[b].first + n * (n - 1) / 2 * d;
   }
   int best = max_seg;
   double best_cost = 0.0;
-  for (int seg = max_seg; seg >= 128; seg >>= 1) {
-    double wgs = 0.0;
-    // a block's segments: of its mean keys (keys mode: a block's rows end together)
+  for (int seg = max_seg; seg >= (paged ? 128 : 64); seg = paged ? seg / 2 : seg - (seg > 1024 ? 256 : 64)) {
+    int64_t wgs = 0;
     for (int b = 0; b < st.n; ++b)
-      wgs += blocks[b] * (keys_mode ? std::ceil(keys[b] / seg) : std::max(1.0, keys[b] / seg + 0.5));
-    const double wg = load + seg, slots = keys_mode ? 1024.0 : 256.0;
-    const double rounds = std::ceil(wgs / slots) * wg;
-    const double even = (wgs * load + all_keys) / slots + 0.5 * wg;
-    const double cost = wgs <= slots ? wg : keys_mode ? rounds : 0.5 * (rounds + even);
+      if (seq[b].n > 0) wgs += floor_sum(seq[b].n, seg, seq[b].step, seq[b].first - 1) + seq[b].n;
+    const double wg = load + seg;
+    const double rounds = std::ceil((double)wgs / slots) * wg;
+    const double even = ((double)wgs * load + (double)all_keys) / slots + 0.5 * wg;
+    const double cost = (double)wgs <= slots ? wg : keys_mode ? rounds : 0.5 * (rounds + even);
     if (seg == max_seg || cost < best_cost) {
       best = seg;
       best_cost = cost;
@@ -360,7 +389,7 @@ static hipError_t run_score(const void* q, const float* qs, const float* w, cons
   const int nrows = rs.i1 - rs.i0;
   const int64_t nblk = (int64_t)st.n * ((nrows + RB - 1) / RB);
   // <= 4096: the key scales of a segment are staged in LDS
-  const int seg = score_segment(st, rs, RB, max_seg, KSPLIT, !KSPLIT && DT == kBf16 ? 256 : 160);
+  const int seg = score_segment(st, rs, RB, max_seg, KSPLIT, DT == kFp8, km.pages != nullptr);
   const int64_t nseg = (lim_max + seg) / seg;
   if (KSPLIT ? (nseg > 0x7FFFFFFF || nblk > 65535) : nseg * nblk > 0x7FFFFFFF)
     return hipErrorInvalidConfiguration;
