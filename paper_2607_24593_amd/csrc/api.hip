@@ -121,6 +121,10 @@ struct Plan {
   size_t off_qlin = 0, off_qlsc = 0, off_plin = 0, off_plsc = 0;  // fp8 epilogue's linear term
   size_t off_rsc = 0;                                              // Refine member scores
   size_t off_sel = 0, sel_bytes = 0;                               // split select scratch
+  // [off_lend, off_scores): regions that hold nothing while score rows of more
+  // than kSplitMaxRows rows are in use (the member scores come after the last
+  // score tile, the split select is for fewer rows); 0 until set
+  size_t off_lend = 0;
   bool qlin = false, plin = false;
   // App. B window and the proxy aggregation
   int W = 0, wkind = PIVOT_WINDOW_SHARED, agg = PIVOT_AGG_MEAN;
@@ -333,19 +337,22 @@ pivot_status make_plan(const pivot_args* a, const pivot_layout* l, int mode, int
     p.off_pw = off;
     off = align_up(off + ng * kH * sizeof(float));
     if (mode == PIVOT_REFINE) {
-      p.off_rsc = off;
-      off = align_up(off + ng * (size_t)g * p.width * score_eb(p.dtype));
       p.off_cand = off;
       if (!ext_cand) off = align_up(off + ng * (size_t)p.width * sizeof(int32_t));
+      p.off_rsc = off;
+      p.off_lend = off;
+      off = align_up(off + ng * (size_t)g * p.width * score_eb(p.dtype));
     }
   }
   if (p.max_nk >= kSplitMinKeys) {  // few long rows per select launch (decode) split over workgroups
     const int64_t rows = (int64_t)p.B * std::max(p.n_q, p.n_groups);
     p.off_sel = off;
+    if (!p.off_lend) p.off_lend = off;
     p.sel_bytes = split_scratch_bytes(std::min<int64_t>(kSplitMaxRows, rows));
     off = align_up(off + p.sel_bytes);
   }
   p.off_scores = off;
+  if (!p.off_lend) p.off_lend = off;
   p.fixed = off;
   return PIVOT_OK;
 }
@@ -450,6 +457,17 @@ pivot_status run_rows(const pivot_args* a, const Plan& p, int kind, int lo, int 
   const int64_t ld_max = ld_for(p.max_nk);
   const int64_t row_bytes = ld_max * score_eb(p.dtype);
   const bool sb16 = bf16_scores(p.dtype);
+  size_t sel_bytes = p.sel_bytes;
+  // A few rows more than the score region holds: the idle regions before it
+  // take them, rather than a last tile of its own (2048 rows of 262144 bf16
+  // scores left one of 8 rows, 90 us of a 3640 us call; 8192 of 65536 one of 16,
+  // 45 us of 2990).
+  const int64_t lend = (int64_t)(p.off_scores - p.off_lend), need = (int64_t)(hi - lo) * row_bytes;
+  if (p.B == 1 && hi - lo > kSplitMaxRows && need > score_bytes && need <= score_bytes + lend) {
+    scores = (uint8_t*)a->workspace + p.off_lend;
+    score_bytes += lend;
+    sel_bytes = 0;
+  }
   int seqs_per_tile, rows_per_tile;
   if (p.B > 1 && score_bytes / (row_bytes * (hi - lo)) >= 1) {
     rows_per_tile = hi - lo;
@@ -493,8 +511,8 @@ pivot_status run_rows(const pivot_args* a, const Plan& p, int kind, int lo, int 
       s = hip_check(timed(PIVOT_KERNEL_SELECT, stream,
                           [&] {
                             return launch_topk(scores, sb16, ld, st, rs, od, lim,
-                                               p.sel_bytes ? (uint8_t*)a->workspace + p.off_sel : nullptr,
-                                               p.sel_bytes, stream);
+                                               sel_bytes ? (uint8_t*)a->workspace + p.off_sel : nullptr, sel_bytes,
+                                               stream);
                           }),
                     "top-k kernel");
       if (s != PIVOT_OK) return s;

@@ -130,3 +130,28 @@ def test_short_segments_paged_equal_contiguous(inputs, fmt, page, g):
         assert np.array_equal(dense[cu[b]:cu[b + 1]], np.sort(host(pv.pivot_dense_index(*one)), 1)), b
         one_r = host(pv.pivot_group_index(*one, mode=pv.PIVOT_REFINE, g=g, c=2 * topk))
         assert np.array_equal(refine[cu[b]:cu[b + 1]], np.sort(one_r, 1)), b
+
+
+@pytest.mark.parametrize("short_rows", [0, 1, 40, 290])
+def test_score_rows_borrow_idle_workspace(short_rows):
+    """A score region a few rows too small: the score tile reaches into the
+    regions that are idle meanwhile (the split select's scratch of a dense call;
+    Refine's member scores too) or, when those do not make up for it, is cut.
+    The sets are those of the full workspace, and nothing past it is written."""
+    x = make_prefill(17000, "fp8", seed=84, threads=8)
+    p0, n_q, topk, g, c = 16100, 900, 300, 3, 1000
+    args = (dev(x.q[p0:p0 + n_q]), dev(x.q_scale[p0:p0 + n_q]), dev(x.w[p0:p0 + n_q]), dev(x.k), dev(x.k_scale), p0,
+            17000, topk)
+    row = ((17000 + 63) // 64 | 1) * 64 * 2
+    say("borrowed rows", short_rows)
+    a = pv.make_args(*args, torch.empty(n_q, topk, dtype=torch.int32, device="cuda"))
+    for kind in ("dense", "refine"):
+        need = pv.pivot_workspace_size(a) if kind == "dense" else \
+            pv.pivot_group_workspace_size(a, pv.group_opts(pv.PIVOT_REFINE, g, c))
+        call = (lambda ws: pv.pivot_dense_index(*args, ws=ws)) if kind == "dense" else \
+            (lambda ws: pv.pivot_group_index(*args, pv.PIVOT_REFINE, g, c, ws=ws))
+        full = np.sort(host(call(torch.empty(need, dtype=torch.uint8, device="cuda"))), 1)
+        less = need - short_rows * row
+        buf = torch.full((less + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        assert np.array_equal(np.sort(host(call(buf[:less])), 1), full), kind
+        assert bool((buf[less:] == 0x5A).all()), kind
