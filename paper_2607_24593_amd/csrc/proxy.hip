@@ -170,6 +170,17 @@ __global__ __launch_bounds__(256) void proxy_kernel(const uint8_t* __restrict__ 
   const int tid = threadIdx.x;
   const int e0 = tid * PER;
 
+  if constexpr (DT == kFp8) {
+    if (gridDim.z > 1) {  // few groups: the members' linear terms in workgroups of their own
+      if (blockIdx.z == 1) {
+        for (int r = tid >> 6; r < gs; r += 4)
+          lin_row(q + (r0 + r) * ROW_BYTES, w + (r0 + r) * kH, q_scale[r0 + r], lo.qlin + (r0 + r) * kLinBytes,
+                  lo.qlsc + (r0 + r) * kLinLevels, tid & 63);
+        return;
+      }
+      lo.qlin = nullptr;
+    }
+  }
   if (gs == 1 || agg != PIVOT_AGG_MEAN) {
     const int64_t rc = r0 + (agg == PIVOT_AGG_LAST ? gs - 1 : 0);
     const uint4* src = reinterpret_cast<const uint4*>(q + rc * ROW_BYTES + e0 * EB);
@@ -330,9 +341,14 @@ hipError_t launch_proxy(int dtype, const void* q, const float* q_scale, const fl
                         const LinOut& lo) {
   if (dtype != kFp8 && (lo.plin || lo.qlin)) return hipErrorInvalidValue;  // linear terms are fp8 only
   if (j1 <= j0 || st.n <= 0) return hipSuccess;
-  dim3 grid((unsigned)(j1 - j0), (unsigned)st.n);
+  // Few groups (decode) leave the GPU empty and wait on the chain mean, members'
+  // terms, proxy's term: the members' terms then go to workgroups of their own
+  // beside it (one group 6.7 -> 5.6 us, 32 groups 8.8 -> 7.2).  From about a
+  // workgroup per CU on, the second read of the rows would cost.
+  const bool apart = dtype == kFp8 && lo.qlin && (int64_t)(j1 - j0) * st.n <= 128;
+  dim3 grid((unsigned)(j1 - j0), (unsigned)st.n, apart ? 2u : 1u);
   // members staged in LDS for their linear terms when one load batch holds a group
-  const int stage = dtype == kFp8 && lo.qlin && agg == PIVOT_AGG_MEAN && g > 1 && g <= 8;
+  const int stage = dtype == kFp8 && lo.qlin && !apart && agg == PIVOT_AGG_MEAN && g > 1 && g <= 8;
   // dynamic LDS: the staged members and their gates, and the proxy's codes (in the first slot)
   const size_t shmem =
       std::max(stage ? (size_t)g * (kH * kD + kH * sizeof(float)) : 0, dtype == kFp8 && lo.plin ? (size_t)kH * kD : 0);
