@@ -38,6 +38,7 @@ struct RowSpace {
   int32_t i0, i1;
   int32_t step;     // position step between consecutive local rows
   int32_t kind;     // kAll, kDenseRows, kProxyRows
+  int32_t shift = 0;  // subtracted from the positions for the row limits (may make early limits negative)
 };
 enum RowKind : int { kAll = 0, kDenseRows = 1, kProxyRows = 2 };
 
@@ -59,7 +60,7 @@ __device__ __forceinline__ int64_t row_index(const SeqTable& st, const RowSpace&
 }
 
 __device__ __forceinline__ int64_t row_limit(const SeqTable& st, const RowSpace& rs, int b, int i) {
-  return (int64_t)st.q_pos0[b] + (int64_t)i * rs.step;
+  return (int64_t)st.q_pos0[b] + (int64_t)i * rs.step - rs.shift;
 }
 
 // Where key s of sequence b of a launch lives in the key arrays: row

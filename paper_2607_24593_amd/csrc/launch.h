@@ -53,14 +53,26 @@ hipError_t launch_lin(const LinRows& set0, const LinRows& set1, hipStream_t stre
 hipError_t launch_lin(const void* q, const float* q_scale, const float* w, int64_t r0, int64_t r1, uint8_t* lin,
                       float* lin_scale, hipStream_t stream);
 
-// Score rows rs (row data [rows, H, d] indexed by row_index(), with lin /
-// lin_scale rows in the same order for fp8) against each sequence's keys
-// 0 .. limit; out [B * (i1 - i0), ld] of fp32, or of bf16 when out_bf16 (fp8
-// inputs only).  lim_max: largest limit of any active row.
-hipError_t launch_score(int dtype, const void* q, const float* q_scale, const float* w, const uint8_t* lin,
-                        const float* lin_scale, const void* k, const float* k_scale, const KeyMap& km,
-                        const SeqTable& st, const RowSpace& rs, int64_t lim_max, void* out, bool out_bf16,
-                        int64_t ld, hipStream_t stream);
+// Score rows of a launch: rows rs (row data [rows, H, d] indexed by row_index(),
+// with lin / lin_scale rows in the same order for fp8) against each sequence's
+// keys 0 .. limit; out [B * (i1 - i0), ld] of fp32, or of bf16 when out_bf16
+// (fp8 inputs only).  lim_max: largest limit of any active row.
+struct ScoreRows {
+  const void* q;
+  const float* q_scale;
+  const float* w;
+  const uint8_t* lin;
+  const float* lin_scale;
+  RowSpace rs;
+  int64_t lim_max;
+  void* out;
+  int64_t ld;
+};
+// With `more` (both sets of at least kScoreRowsMode rows): a second set of rows
+// over the same keys in the same launch.
+constexpr int kScoreRowsMode = 16;
+hipError_t launch_score(int dtype, const ScoreRows& rows, const ScoreRows* more, const void* k, const float* k_scale,
+                        const KeyMap& km, const SeqTable& st, bool out_bf16, hipStream_t stream);
 
 // Top-m of score rows (fp32, or bf16 when scores_bf16): row (b, i) has
 // limit + 1 valid entries; lim_max is the largest limit.  Up to 256 long rows
@@ -70,6 +82,18 @@ hipError_t launch_score(int dtype, const void* q, const float* q_scale, const fl
 hipError_t launch_topk(const void* scores, bool scores_bf16, int64_t ld, const SeqTable& st, const RowSpace& rs,
                        const OutDesc& od, int64_t lim_max, void* scratch, size_t scratch_bytes,
                        hipStream_t stream);
+// Two sets of rows at once, where one select kernel takes them both
+// (topk_both_ok); scores, ld, rs, od and lim_max of each as in launch_topk.
+struct TopkRows {
+  const void* scores;
+  int64_t ld;
+  RowSpace rs;
+  OutDesc od;
+  int64_t lim_max;
+};
+bool topk_both_ok(bool scores_bf16, const SeqTable& st, const TopkRows& a, const TopkRows& b);
+hipError_t launch_topk_both(bool scores_bf16, const SeqTable& st, const TopkRows& a, const TopkRows& b,
+                            hipStream_t stream);
 size_t split_scratch_bytes(int64_t rows);
 constexpr int kSplitMaxRows = 256;   // launches with more rows do not split
 constexpr int kSplitMinKeys = 16384; // nor do launches whose rows are all shorter

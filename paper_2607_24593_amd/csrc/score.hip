@@ -48,17 +48,27 @@ constexpr int kPieces = kStageKeys<DT> / kPassKeys<DT>;
 template <int DT>
 constexpr int kStageSlot = kStageKeys<DT> * (kD * (DT == kFp8 ? 1 : 2) + 16);
 
+// A launch's rows as the kernel takes them (ScoreRows).
+struct RowArgs {
+  const uint8_t* q;
+  const float* q_scale;
+  const float* w;
+  const uint8_t* lin;
+  const float* lin_scale;
+  RowSpace rs;
+  void* out;
+  int64_t ld;
+};
+
 // OB16: scores leave as bf16 (RNE) instead of fp32.
+// Rows mode takes two sets of rows (workgroups [0, wgs0) the first): the
+// guardrail's dense rows fill the CUs that the proxies' last workgroups leave
+// idle, where a launch of their own would have added a tail.
 template <int DT, int R, bool KSPLIT, bool PAGED, bool OB16>
-__global__ __launch_bounds__(256) void score_kernel(const uint8_t* __restrict__ q,
-                                                    const float* __restrict__ q_scale,
-                                                    const float* __restrict__ w,
-                                                    const uint8_t* __restrict__ lin,
-                                                    const float* __restrict__ lin_scale,
+__global__ __launch_bounds__(256) void score_kernel(RowArgs set0, RowArgs set1, uint32_t wgs0,
                                                     const uint8_t* __restrict__ k,
-                                                    const float* __restrict__ k_scale, KeyMap km,
-                                                    SeqTable st, RowSpace rs, void* __restrict__ out,
-                                                    int64_t ld, int seg_keys) {
+                                                    const float* __restrict__ k_scale, KeyMap km, SeqTable st,
+                                                    int seg_keys) {
   constexpr int SE = OB16 ? 2 : 4;  // bytes per score
   using Tile = RowTile<DT, R>;
   constexpr int EB = Tile::EB;
@@ -73,11 +83,21 @@ __global__ __launch_bounds__(256) void score_kernel(const uint8_t* __restrict__ 
                                             // starts on a page boundary or lies inside one page)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
+  const bool second = !KSPLIT && blockIdx.x >= wgs0;
+  const uint8_t* const q = second ? set1.q : set0.q;
+  const float* const q_scale = second ? set1.q_scale : set0.q_scale;
+  const float* const w = second ? set1.w : set0.w;
+  const uint8_t* const lin = second ? set1.lin : set0.lin;
+  const float* const lin_scale = second ? set1.lin_scale : set0.lin_scale;
+  const RowSpace rs = second ? set1.rs : set0.rs;
+  void* const out = second ? set1.out : set0.out;
+  const int64_t ld = second ? set1.ld : set0.ld;
+  const uint32_t bx = blockIdx.x - (second ? wgs0 : 0u);
   const int nrows = rs.i1 - rs.i0;
   const int nbps = (nrows + RB - 1) / RB;
   const uint32_t nblk = (uint32_t)(st.n * nbps);
-  const uint32_t yb = KSPLIT ? blockIdx.y : blockIdx.x % nblk;  // row block
-  const uint32_t xs = KSPLIT ? blockIdx.x : blockIdx.x / nblk;  // key segment
+  const uint32_t yb = KSPLIT ? blockIdx.y : bx % nblk;  // row block
+  const uint32_t xs = KSPLIT ? blockIdx.x : bx / nblk;  // key segment
   const int b = (int)(yb / nbps);
   if (b >= st.n) return;
   const int i_blk = rs.i0 + (int)(yb % nbps) * RB;
@@ -315,9 +335,11 @@ static int64_t floor_sum(int64_t n, int64_t m, int64_t b, int64_t a) {
   return s;
 }
 
-// The key segment of a launch: the length with the shortest estimated time, a
-// multiple of 64 keys up to max_seg (paged keys: a power of two of at least 128,
-// so that a segment starts on a page boundary or lies inside one page).  A
+// The key segment of a launch: the length with the shortest estimated time up
+// to max_seg: in keys mode a multiple of 64 keys, in rows mode a multiple of 256
+// (the lengths between measured slower than both neighbours) or 64 or 128; with
+// paged keys a power of two of at least 128, so that a segment starts on a page
+// boundary or lies inside one page.  A
 // workgroup costs its prologue (row tile, scales, first keys: as much as scoring
 // `load` keys) and its keys.
 //   Rows mode (MFMA bound): launches of a few workgroups per CU run in rounds
@@ -333,41 +355,46 @@ static int64_t floor_sum(int64_t n, int64_t m, int64_t b, int64_t a) {
 //     fp8, 8192 queries at 128K, groups of 4  [1780] / 1812 / 1868 /  -  /  -  /  -
 //     fp8, 500 rows of 20K keys                  -  /   -  /   -  / [94] / 113 /  -
 //     bf16, 1025 rows of 24K keys (max 2048)     -  / [667] / 683 /  -  /  -  /  -
-//     bf16, 2048 queries from 0                  -  /   -  /   -  / 101 /  95 /  94
+//     bf16, 2048 queries from 0                  -  /   -  /   -  / [74] /  74 /  82
+//       (192, 320 and 384 keys: 79, 81, 78)
 //     fp8, 24 decode rows of 5K-70K keys         -  / 64 / [50.7] / 55.2 / - / -
 //     bf16, 8 decode rows of 40K keys            -  / 80 / 74.4 / 72.7 / 76.5 / 92
 //   and at 640 keys [69.5]; 500 rows of 20K keys at 1280 and 2560 keys 90, [91];
 //   fp8, 32 decode rows of 128K keys at 2048, 1536 and 1024 keys [159.6], 163, 164.5
-static int score_segment(const SeqTable& st, const RowSpace& rs, int rb, int max_seg, bool keys_mode, bool fp8,
-                         bool paged) {
+static int score_segment(const SeqTable& st, const RowSpace& rs0, const RowSpace* rs1, int rb, int max_seg,
+                         bool keys_mode, bool fp8, bool paged) {
   const int load = keys_mode || fp8 ? 160 : 256;
   const double slots = !keys_mode ? 256.0 : fp8 ? 1024.0 : 512.0;
   struct Blocks {
     int64_t n, first, step;  // row blocks, keys of the first one, keys more per block
-  } seq[kMaxSeq];
+  } seq[2 * kMaxSeq];
   int64_t all_keys = 0;
-  for (int b = 0; b < st.n; ++b) {
+  const int n_seq = rs1 ? 2 * st.n : st.n;
+  for (int u = 0; u < n_seq; ++u) {
+    const int b = u % st.n;
+    const RowSpace& rs = u < st.n ? rs0 : *rs1;
     const int cnt = rs.kind == kProxyRows ? (st.n_rows[b] + rs.step - 1) / rs.step : st.n_rows[b];
     int hi = std::min(rs.i1, cnt), lo = rs.i0;
     if (rs.kind == kDenseRows) hi = std::min(hi, st.dense_rows[b]);
     if (rs.kind == kProxyRows) lo = std::max(lo, st.first_proxy[b]);
-    seq[b] = Blocks{0, 0, 0};
+    seq[u] = Blocks{0, 0, 0};
     if (hi <= lo) continue;
     const int64_t b0 = (lo - rs.i0) / rb, b1 = (hi - 1 - rs.i0) / rb;
     // a block scans the keys of its last row; the last block's last row is hi - 1
     const int64_t end0 = std::min<int64_t>(rs.i0 + (b0 + 1) * rb, hi) - 1;
-    const int64_t k0 = st.q_pos0[b] + end0 * rs.step + 1, d = (int64_t)rb * rs.step;
+    const int64_t k0 = st.q_pos0[b] - rs.shift + end0 * rs.step + 1, d = (int64_t)rb * rs.step;
     const int64_t skip = k0 > 0 ? 0 : d > 0 ? (-k0) / d + 1 : b1 - b0 + 1;  // blocks with no key in reach
     const int64_t n = std::max<int64_t>(0, b1 - b0 + 1 - skip);
-    seq[b] = Blocks{n, k0 + skip * d, d};
-    all_keys += n * seq[b].first + n * (n - 1) / 2 * d;
+    seq[u] = Blocks{n, k0 + skip * d, d};
+    all_keys += n * seq[u].first + n * (n - 1) / 2 * d;
   }
   int best = max_seg;
   double best_cost = 0.0;
-  for (int seg = max_seg; seg >= (paged ? 128 : 64); seg = paged ? seg / 2 : seg - (seg > 1024 ? 256 : 64)) {
+  auto shorter = [&](int seg) { return paged || (!keys_mode && seg <= 256) ? seg / 2 : seg - (keys_mode ? 64 : 256); };
+  for (int seg = max_seg; seg >= (paged ? 128 : 64); seg = shorter(seg)) {
     int64_t wgs = 0;
-    for (int b = 0; b < st.n; ++b)
-      if (seq[b].n > 0) wgs += floor_sum(seq[b].n, seg, seq[b].step, seq[b].first - 1) + seq[b].n;
+    for (int u = 0; u < n_seq; ++u)
+      if (seq[u].n > 0) wgs += floor_sum(seq[u].n, seg, seq[u].step, seq[u].first - 1) + seq[u].n;
     const double wg = load + seg;
     const double rounds = std::ceil((double)wgs / slots) * wg;
     const double even = ((double)wgs * load + (double)all_keys) / slots + 0.5 * wg;
@@ -381,66 +408,55 @@ static int score_segment(const SeqTable& st, const RowSpace& rs, int rb, int max
 }
 
 template <int DT, int R, bool KSPLIT, bool OB16>
-static hipError_t run_score(const void* q, const float* qs, const float* w, const uint8_t* lin, const float* lsc,
-                            const void* k, const float* ks, const KeyMap& km, const SeqTable& st,
-                            const RowSpace& rs, int64_t lim_max, void* out, int64_t ld, int max_seg,
-                            hipStream_t stream) {
+static hipError_t run_score(const ScoreRows& s, const ScoreRows* more, const void* k, const float* ks,
+                            const KeyMap& km, const SeqTable& st, int max_seg, hipStream_t stream) {
   constexpr int RB = KSPLIT ? R : 4 * R;
-  const int nrows = rs.i1 - rs.i0;
-  const int64_t nblk = (int64_t)st.n * ((nrows + RB - 1) / RB);
   // <= 4096: the key scales of a segment are staged in LDS
-  const int seg = score_segment(st, rs, RB, max_seg, KSPLIT, DT == kFp8, km.pages != nullptr);
-  const int64_t nseg = (lim_max + seg) / seg;
-  if (KSPLIT ? (nseg > 0x7FFFFFFF || nblk > 65535) : nseg * nblk > 0x7FFFFFFF)
+  const int seg = score_segment(st, s.rs, more ? &more->rs : nullptr, RB, max_seg, KSPLIT, DT == kFp8,
+                                km.pages != nullptr);
+  auto blocks = [&](const ScoreRows& x) { return (int64_t)st.n * ((x.rs.i1 - x.rs.i0 + RB - 1) / RB); };
+  auto segs = [&](const ScoreRows& x) { return (x.lim_max + seg) / seg; };
+  const int64_t nblk = blocks(s), nseg = segs(s), wgs1 = more ? blocks(*more) * segs(*more) : 0;
+  if (KSPLIT ? (more || nseg > 0x7FFFFFFF || nblk > 65535) : nseg * nblk + wgs1 > 0x7FFFFFFF)
     return hipErrorInvalidConfiguration;
-  const dim3 grid = KSPLIT ? dim3((unsigned)nseg, (unsigned)nblk) : dim3((unsigned)(nseg * nblk));
+  const dim3 grid = KSPLIT ? dim3((unsigned)nseg, (unsigned)nblk) : dim3((unsigned)(nseg * nblk + wgs1));
+  auto args = [](const ScoreRows& x) {
+    return RowArgs{(const uint8_t*)x.q, x.q_scale, x.w, x.lin, x.lin_scale, x.rs, x.out, x.ld};
+  };
+  const RowArgs a0 = args(s), a1 = more ? args(*more) : a0;
+  const uint32_t wgs0 = (uint32_t)(nseg * nblk);
   if (km.pages)
-    hipLaunchKernelGGL((score_kernel<DT, R, KSPLIT, true, OB16>), grid, dim3(256), 0, stream, (const uint8_t*)q, qs,
-                       w, lin, lsc, (const uint8_t*)k, ks, km, st, rs, out, ld, seg);
+    hipLaunchKernelGGL((score_kernel<DT, R, KSPLIT, true, OB16>), grid, dim3(256), 0, stream, a0, a1, wgs0,
+                       (const uint8_t*)k, ks, km, st, seg);
   else
-    hipLaunchKernelGGL((score_kernel<DT, R, KSPLIT, false, OB16>), grid, dim3(256), 0, stream, (const uint8_t*)q, qs,
-                       w, lin, lsc, (const uint8_t*)k, ks, km, st, rs, out, ld, seg);
+    hipLaunchKernelGGL((score_kernel<DT, R, KSPLIT, false, OB16>), grid, dim3(256), 0, stream, a0, a1, wgs0,
+                       (const uint8_t*)k, ks, km, st, seg);
   return hipGetLastError();
 }
 
 template <bool OB16>
-static hipError_t score_fp8(const void* q, const float* q_scale, const float* w, const uint8_t* lin,
-                            const float* lin_scale, const void* k, const float* k_scale, const KeyMap& km,
-                            const SeqTable& st, const RowSpace& rs, int64_t lim_max, void* out, int64_t ld,
-                            hipStream_t stream) {
-  const int nrows = rs.i1 - rs.i0;
-  if (nrows >= 16)
-    return run_score<kFp8, 4, false, OB16>(q, q_scale, w, lin, lin_scale, k, k_scale, km, st, rs, lim_max, out,
-                                           ld, 4096, stream);
-  if (nrows == 1)
-    return run_score<kFp8, 1, true, OB16>(q, q_scale, w, lin, lin_scale, k, k_scale, km, st, rs, lim_max, out,
-                                          ld, 2048, stream);
-  if (nrows == 2)
-    return run_score<kFp8, 2, true, OB16>(q, q_scale, w, lin, lin_scale, k, k_scale, km, st, rs, lim_max, out,
-                                          ld, 2048, stream);
-  return run_score<kFp8, 4, true, OB16>(q, q_scale, w, lin, lin_scale, k, k_scale, km, st, rs, lim_max, out, ld,
-                                        2048, stream);
+static hipError_t score_fp8(const ScoreRows& s, const ScoreRows* more, const void* k, const float* k_scale,
+                            const KeyMap& km, const SeqTable& st, hipStream_t stream) {
+  const int nrows = s.rs.i1 - s.rs.i0;
+  if (nrows >= kScoreRowsMode) return run_score<kFp8, 4, false, OB16>(s, more, k, k_scale, km, st, 4096, stream);
+  if (nrows == 1) return run_score<kFp8, 1, true, OB16>(s, more, k, k_scale, km, st, 2048, stream);
+  if (nrows == 2) return run_score<kFp8, 2, true, OB16>(s, more, k, k_scale, km, st, 2048, stream);
+  return run_score<kFp8, 4, true, OB16>(s, more, k, k_scale, km, st, 2048, stream);
 }
 
-hipError_t launch_score(int dtype, const void* q, const float* q_scale, const float* w, const uint8_t* lin,
-                        const float* lin_scale, const void* k, const float* k_scale, const KeyMap& km,
-                        const SeqTable& st, const RowSpace& rs, int64_t lim_max, void* out, bool out_bf16,
-                        int64_t ld, hipStream_t stream) {
-  const int nrows = rs.i1 - rs.i0;
-  if (nrows <= 0 || lim_max < 0 || st.n <= 0) return hipSuccess;
+hipError_t launch_score(int dtype, const ScoreRows& s, const ScoreRows* more, const void* k, const float* k_scale,
+                        const KeyMap& km, const SeqTable& st, bool out_bf16, hipStream_t stream) {
+  const int nrows = s.rs.i1 - s.rs.i0;
+  if (nrows <= 0 || s.lim_max < 0 || st.n <= 0) return hipSuccess;
+  if (more && (nrows < kScoreRowsMode || more->rs.i1 - more->rs.i0 < kScoreRowsMode || more->lim_max < 0))
+    return hipErrorInvalidValue;
   if (dtype == kFp8)
-    return out_bf16 ? score_fp8<true>(q, q_scale, w, lin, lin_scale, k, k_scale, km, st, rs, lim_max, out, ld, stream)
-                    : score_fp8<false>(q, q_scale, w, lin, lin_scale, k, k_scale, km, st, rs, lim_max, out, ld,
-                                       stream);
+    return out_bf16 ? score_fp8<true>(s, more, k, k_scale, km, st, stream)
+                    : score_fp8<false>(s, more, k, k_scale, km, st, stream);
   if (out_bf16) return hipErrorInvalidValue;  // bf16 inputs keep fp32 scores
-  if (nrows >= 16)
-    return run_score<kBf16, 2, false, false>(q, nullptr, w, nullptr, nullptr, k, nullptr, km, st, rs, lim_max,
-                                             out, ld, 2048, stream);
-  if (nrows == 1)
-    return run_score<kBf16, 1, true, false>(q, nullptr, w, nullptr, nullptr, k, nullptr, km, st, rs, lim_max,
-                                            out, ld, 2048, stream);
-  return run_score<kBf16, 2, true, false>(q, nullptr, w, nullptr, nullptr, k, nullptr, km, st, rs, lim_max, out,
-                                          ld, 2048, stream);
+  if (nrows >= kScoreRowsMode) return run_score<kBf16, 2, false, false>(s, more, k, nullptr, km, st, 2048, stream);
+  if (nrows == 1) return run_score<kBf16, 1, true, false>(s, more, k, nullptr, km, st, 2048, stream);
+  return run_score<kBf16, 2, true, false>(s, more, k, nullptr, km, st, 2048, stream);
 }
 
 }  // namespace pivot

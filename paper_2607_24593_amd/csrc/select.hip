@@ -842,6 +842,16 @@ struct ResidentCands {
   }
 };
 
+// A set of rows of a resident select launch; blocks [0, blocks0) take the
+// first, the others the second (the proxies' rows and the guardrail's).
+template <class E>
+struct SelectRows {
+  const E* scores;
+  int64_t ld;
+  RowSpace rs;
+  OutDesc od;
+};
+
 // Rows of at most T V N scores (N = 8 bf16 or 4 fp32 to a 16-byte vector): one
 // workgroup per row requests all of it at once, V vectors per thread.
 //   1 threshold  wave w's vector w mod vn (vn vectors in use) is the sample,
@@ -872,7 +882,7 @@ struct ResidentCands {
 // row does not fit the registers of one workgroup.
 template <int T, int V, int CAP, class E, bool FILTER>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 && V * (int)sizeof(E) <= 16 ? 8 : 4)))
-void topk_resident_kernel(const E* __restrict__ scores, int64_t ld, SeqTable st, RowSpace rs, OutDesc od) {
+void topk_resident_kernel(SelectRows<E> set0, SelectRows<E> set1, int blocks0, SeqTable st) {
   using OK = OrderKey<E>;
   constexpr int N = ScoreVec<E>::N;
   constexpr bool WORD = sizeof(E) == 2 && T * V * N <= 65536;
@@ -886,9 +896,15 @@ void topk_resident_kernel(const E* __restrict__ scores, int64_t ld, SeqTable st,
   __shared__ uint16_t vlist[FILTER ? T * V : 1];  // vectors with a key that reaches the threshold
   __shared__ SelectShared sel;
   __shared__ int32_t lcount, kept, listed;
+  const bool second = (int)blockIdx.x >= blocks0;
+  const E* const scores = second ? set1.scores : set0.scores;
+  const int64_t ld = second ? set1.ld : set0.ld;
+  const RowSpace rs = second ? set1.rs : set0.rs;
+  const OutDesc od = second ? set1.od : set0.od;
+  const int bx = (int)blockIdx.x - (second ? blocks0 : 0);
   const int nrows = rs.i1 - rs.i0;
-  const int b = blockIdx.x / nrows;
-  const int i = rs.i0 + blockIdx.x % nrows;
+  const int b = bx / nrows;
+  const int i = rs.i0 + bx % nrows;
   if (!row_active(st, rs, b, i)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1276,9 +1292,58 @@ static int64_t min_limit(const SeqTable& st, const RowSpace& rs) {
     int hi = std::min(rs.i1, cnt), lo = rs.i0;
     if (rs.kind == kDenseRows) hi = std::min(hi, st.dense_rows[b]);
     if (rs.kind == kProxyRows) lo = std::max(lo, st.first_proxy[b]);
-    if (hi > lo) lim = std::min(lim, (int64_t)st.q_pos0[b] + (int64_t)lo * rs.step);
+    if (hi > lo) lim = std::min(lim, (int64_t)st.q_pos0[b] + (int64_t)lo * rs.step - rs.shift);
   }
   return lim;
+}
+
+// Scores of a row that a 512-thread workgroup holds: 8 (bf16) or 16 (fp32) vectors a thread.
+constexpr int64_t kResident = 32768;
+
+// `blocks` rows of `set`, then `more_blocks` of `more`.
+template <int T, int V, class E>
+static hipError_t resident_launch(const SelectRows<E>& set, const SelectRows<E>* more, int blocks, int more_blocks,
+                                  const SeqTable& st, hipStream_t stream) {
+  constexpr bool kFilter = T == kSelThreadsWide;
+  const SelectRows<E>& second = more ? *more : set;
+  const dim3 grid((unsigned)(blocks + more_blocks));
+  if (std::max(set.od.m, second.od.m) <= kSelCapSmall / 2)
+    hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCapSmall, E, kFilter>), grid, dim3(T), 0, stream, set, second,
+                       blocks, st);
+  else
+    hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCap16, E, kFilter>), grid, dim3(T), 0, stream, set, second,
+                       blocks, st);
+  return hipGetLastError();
+}
+
+// Rows of at most kResident scores.
+template <class E>
+static hipError_t resident_512(const SelectRows<E>& set, const SelectRows<E>* more, int blocks, int more_blocks,
+                               int64_t lim_max, const SeqTable& st, hipStream_t stream) {
+  constexpr int V = 32 / ScoreVec<E>::N * 2;  // vectors of a thread that make kResident
+  if constexpr (sizeof(E) == 4)
+    if (lim_max + 1 <= kResident / 2)
+      return resident_launch<kSelThreads, V / 2, E>(set, more, blocks, more_blocks, st, stream);
+  return resident_launch<kSelThreads, V, E>(set, more, blocks, more_blocks, st, stream);
+}
+
+bool topk_both_ok(bool, const SeqTable& st, const TopkRows& a, const TopkRows& b) {
+  const int64_t rows = (int64_t)st.n * ((a.rs.i1 - a.rs.i0) + (b.rs.i1 - b.rs.i0));
+  return rows > kWideMaxRows && rows <= 0x7FFFFFFF && a.od.m <= kResidentMaxM && b.od.m <= kResidentMaxM &&
+         std::max(a.lim_max, b.lim_max) + 1 <= kResident;
+}
+
+template <class E>
+static hipError_t topk_both(const SeqTable& st, const TopkRows& a, const TopkRows& b, hipStream_t stream) {
+  const SelectRows<E> s0{static_cast<const E*>(a.scores), a.ld, a.rs, a.od};
+  const SelectRows<E> s1{static_cast<const E*>(b.scores), b.ld, b.rs, b.od};
+  return resident_512<E>(s0, &s1, st.n * (a.rs.i1 - a.rs.i0), st.n * (b.rs.i1 - b.rs.i0),
+                      std::max(a.lim_max, b.lim_max), st, stream);
+}
+
+hipError_t launch_topk_both(bool scores_bf16, const SeqTable& st, const TopkRows& a, const TopkRows& b,
+                            hipStream_t stream) {
+  return scores_bf16 ? topk_both<bf16_t>(st, a, b, stream) : topk_both<float>(st, a, b, stream);
 }
 
 template <class E>
@@ -1290,37 +1355,26 @@ static hipError_t topk_launch(const E* scores, int64_t ld, const SeqTable& st, c
   const int64_t blocks = (int64_t)st.n * nrows;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   constexpr int N = ScoreVec<E>::N;
-  constexpr int64_t kResident = 32768;  // scores of a 512-thread workgroup's row: 8 (bf16) or 16 (fp32) vectors a thread
-  const int cap_small = od.m <= kSelCapSmall / 2;
-#define PIVOT_RESIDENT(T, V)                                                                                      \
-  do {                                                                                                            \
-    if (cap_small)                                                                                                \
-      hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCapSmall, E, T == kSelThreadsWide>), dim3((unsigned)blocks), dim3(T), 0,       \
-                         stream, scores, ld, st, rs, od);                                                         \
-    else                                                                                                          \
-      hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCap16, E, T == kSelThreadsWide>), dim3((unsigned)blocks), dim3(T), 0, stream,   \
-                         scores, ld, st, rs, od);                                                                 \
-    return hipGetLastError();                                                                                     \
-  } while (0)
   if (od.m <= kResidentMaxM) {
+    const SelectRows<E> set{scores, ld, rs, od};
     // few rows (decode): a wide workgroup holds up to 131072 bf16 or 65536 fp32 scores
-    if (blocks <= kWideMaxRows && lim_max + 1 <= 16 * kSelThreadsWide * N) PIVOT_RESIDENT(kSelThreadsWide, 16);
-    if (sizeof(E) == 4 && lim_max + 1 <= kResident / 2) PIVOT_RESIDENT(kSelThreads, 8);
-    if (lim_max + 1 <= kResident) PIVOT_RESIDENT(kSelThreads, 32 / N * 2);
+    if (blocks <= kWideMaxRows && lim_max + 1 <= 16 * kSelThreadsWide * N)
+      return resident_launch<kSelThreadsWide, 16, E>(set, nullptr, (int)blocks, 0, st, stream);
+    if (lim_max + 1 <= kResident) return resident_512<E>(set, nullptr, (int)blocks, 0, lim_max, st, stream);
     // one sequence whose rows grow past that: its shorter rows on their own
     if (st.n == 1 && rs.step > 0) {
-      const int64_t first = (kResident - 1 - st.q_pos0[0]) / rs.step + 1;  // first row longer than kResident
+      const int64_t p0 = (int64_t)st.q_pos0[0] - rs.shift;
+      const int64_t first = (kResident - 1 - p0) / rs.step + 1;  // first row longer than kResident
       if (first - rs.i0 >= kWideMaxRows && first < rs.i1) {
         RowSpace lo = rs, hi = rs;
         lo.i1 = hi.i0 = (int32_t)first;
-        const int64_t lim_lo = std::min<int64_t>(lim_max, st.q_pos0[0] + (first - 1) * rs.step);
+        const int64_t lim_lo = std::min<int64_t>(lim_max, p0 + (first - 1) * rs.step);
         const hipError_t e = topk_launch(scores, ld, st, lo, od, lim_lo, scratch, scratch_bytes, stream);
         if (e != hipSuccess) return e;
         return topk_launch(scores + (first - rs.i0) * ld, ld, st, hi, od, lim_max, scratch, scratch_bytes, stream);
       }
     }
   }
-#undef PIVOT_RESIDENT
   if (blocks <= kWideMaxRows && lim_max + 1 >= kSampleMinLen && scratch &&
       scratch_bytes >= split_scratch_bytes(blocks)) {
     // few long rows: P slice workgroups per row, then one merge workgroup

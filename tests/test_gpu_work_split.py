@@ -155,3 +155,43 @@ def test_score_rows_borrow_idle_workspace(short_rows):
         buf = torch.full((less + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
         assert np.array_equal(np.sort(host(call(buf[:less])), 1), full), kind
         assert bool((buf[less:] == 0x5A).all()), kind
+
+
+@pytest.mark.parametrize("fmt,p0,n_q,g,c,topk,window", [
+    ("fp8", 0, 6001, 4, 2048, 500, 0),     # guardrail rows and proxies in one scoring and one select launch
+    ("fp8", 0, 7000, 8, 4096, 2048, 4),    # the shared window's shifted limits beside unshifted ones
+    ("bf16", 0, 2047, 3, 512, 200, 0),     # 171 guardrail groups, the last one cut by the threshold
+    ("bf16", 900, 1200, 2, 1024, 300, 3),  # 124 dense rows
+    ("fp8", 500, 560, 4, 520, 100, 0),     # 20 dense rows
+    ("fp8", 500, 540, 4, 990, 100, 0),     # 12 proxies: apart
+])
+@pytest.mark.parametrize("mode", ["reuse", "refine"])
+def test_guardrail_beside_proxies(inputs, fmt, p0, n_q, g, c, topk, window, mode):
+    """Calls with groups on both sides of the guardrail against the oracle (the
+    sampled groups include both sides of it), and the same sets when the
+    workspace has no room for both score tiles at once."""
+    if window and mode == "reuse":
+        pytest.skip("the window applies to Refine")
+    x, n_k, ng = inputs[fmt], p0 + n_q, -(-n_q // g)
+    say("guardrail", fmt, n_q, g, c, mode)
+    qs = None if x.q_scale is None else x.q_scale[p0:n_k]
+    ks = None if x.k_scale is None else x.k_scale[:n_k]
+    args = (dev(x.q[p0:n_k]), dev(qs), dev(x.w[p0:n_k]), dev(x.k[:n_k]), dev(ks), p0, n_k, topk)
+    m = pv.PIVOT_REFINE if mode == "refine" else pv.PIVOT_REUSE
+    cand = torch.full((1, ng, c), -7, dtype=torch.int32, device="cuda") if mode == "refine" else None
+    got = host(pv.pivot_group_index_opts(*args, m, g, c, window=window, out_cand=cand))
+    if not window:
+        edge = -(-(c - p0) // g)
+        groups = sorted({0, edge - 1, edge, edge + 1, ng - 1} | set(range(0, ng, max(1, ng // 7))))
+        check_pivot(fmt, x.q[p0:n_k], qs, x.w[p0:n_k], p0, x.k[:n_k], ks, n_k,
+                    mode=oracle.REFINE if mode == "refine" else oracle.REUSE, g=g, c=c, topk=topk, dense_below=-1,
+                    gpu_idx=got, gpu_cand=None if cand is None else host(cand)[0],
+                    groups=[j for j in groups if 0 <= j < ng], label="guardrail")
+    a = pv.make_args(*args, torch.empty(n_q, topk, dtype=torch.int32, device="cuda"))
+    o = pv.group_opts(m, g, c, window=window)
+    need = pv.pivot_group_workspace_size(a, o)
+    row = ((n_k + 63) // 64 | 1) * 64 * (2 if fmt == "fp8" else 4)
+    rows = min(max(-(-max(0, c - p0) // g) * g, ng - max(0, -(-(c - p0) // g))) - 16, 400)  # a score region of 16 rows and up
+    small = torch.empty(need - max(0, rows) * row, dtype=torch.uint8, device="cuda")
+    one = host(pv.pivot_group_index_opts(*args, m, g, c, window=window, ws=small))
+    assert np.array_equal(np.sort(one, 1), np.sort(got, 1))
