@@ -535,18 +535,11 @@ pivot_status check_workspace(const pivot_args* a, const Plan& p, int64_t& score_
   return PIVOT_OK;
 }
 
-// Query rows that need the fp8 linear term (mfma_tile.h): the leading dense
-// rows of a single sequence, else every row (a batch, or Refine re-scoring
-// the members).
-int64_t query_lin_rows(const Plan& p) {
-  return (p.B == 1 && p.mode != PIVOT_REFINE) ? p.dense_hi : p.rows_total;
-}
-
+// The fp8 linear terms (mfma_tile.h) of every query row of a dense call.
 pivot_status query_lin(const pivot_args* a, const Plan& p, uint8_t* ws, hipStream_t stream) {
   if (!p.qlin) return PIVOT_OK;
-  const int64_t rows = query_lin_rows(p);
   return hip_check(timed(PIVOT_KERNEL_LIN, stream, [&] {
-                     return launch_lin(a->q, a->q_scale, a->w, 0, rows, ws + p.off_qlin,
+                     return launch_lin(a->q, a->q_scale, a->w, p.rows_total, ws + p.off_qlin,
                                        reinterpret_cast<float*>(ws + p.off_qlsc), stream);
                    }),
                    "linear-term kernel");
@@ -675,14 +668,13 @@ pivot_status group_index(const pivot_args* a, const pivot_layout* l, const pivot
   const float* qs = p.dtype == PIVOT_DT_FP8_E4M3 ? a->q_scale : nullptr;
 
   // fp8 linear terms (mfma_tile.h): the proxy kernel writes those of the
-  // proxies, and for Refine those of the members it reads, unless some
-  // sequence of a batch also has dense rows (then every query row is done by
-  // the linear-term kernel, which needs a contiguous range)
+  // proxies, and for Refine those of the members it reads; the dense rows of
+  // each sequence have a launch of their own
   uint8_t* plin = p.plin ? ws + p.off_plin : nullptr;
   float* plsc = p.plin ? reinterpret_cast<float*>(ws + p.off_plsc) : nullptr;
   uint8_t* qlin = p.qlin ? ws + p.off_qlin : nullptr;
   float* qlsc = p.qlin ? reinterpret_cast<float*>(ws + p.off_qlsc) : nullptr;
-  const bool member_lin = p.plin && p.qlin && mode == PIVOT_REFINE && (p.B == 1 || p.dense_hi == 0);
+  const bool member_lin = p.plin && p.qlin && mode == PIVOT_REFINE;
   if (p.any_proxy)
     for (int b0 = 0; b0 < p.B; b0 += kMaxSeq) {  // Eq. 4 proxies (or the first / last member)
       const int nb = std::min(kMaxSeq, p.B - b0);
@@ -708,18 +700,18 @@ pivot_status group_index(const pivot_args* a, const pivot_layout* l, const pivot
       if (s != PIVOT_OK) return s;
     }
 
-  // the remaining query rows' linear terms: the dense rows, or every row
-  if (p.qlin) {
-    const int64_t rows = member_lin ? (p.B == 1 ? p.dense_hi : 0) : query_lin_rows(p);
-    if (rows > 0) {
+  if (p.qlin && p.dense_hi > 0)
+    for (int b0 = 0; b0 < p.B; b0 += kMaxSeq) {
+      const SeqTable st = table_for(p, b0, std::min(kMaxSeq, p.B - b0));
+      const size_t qoff = (size_t)p.row0[b0];
       s = hip_check(timed(PIVOT_KERNEL_LIN, stream, [&] {
-                      return launch_lin(LinRows{(const uint8_t*)a->q, a->q_scale, a->w, 0, rows, qlin, qlsc},
-                                        LinRows{}, stream);
+                      return launch_lin_dense((const uint8_t*)a->q + qoff * p.row_bytes, a->q_scale + qoff,
+                                              a->w + qoff * kH, st, qlin + qoff * kLinBytes,
+                                              qlsc + qoff * kLinLevels, stream);
                     }),
                     "linear-term kernel");
       if (s != PIVOT_OK) return s;
     }
-  }
 
   // Eq. 5 proxy scan, then Eq. 6 (Reuse: top-k shared by the members) or
   // Eq. 7 (Refine: top-c candidates; before a shared window, the top c - W - g + 1
@@ -1047,7 +1039,7 @@ pivot_status pivot_score_rows(int32_t dtype, int32_t heads, int32_t dim, int32_t
   st.n_rows[0] = n_rows;
   RowSpace rs{0, n_rows, lim_step, kAll};
   if (fp8) {
-    pivot_status s = hip_check(launch_lin(q, q_scale, w, 0, n_rows, lin, lsc, (hipStream_t)stream),
+    pivot_status s = hip_check(launch_lin(q, q_scale, w, n_rows, lin, lsc, (hipStream_t)stream),
                                "linear-term kernel");
     if (s != PIVOT_OK) return s;
   }

@@ -38,20 +38,13 @@ hipError_t launch_proxy(int dtype, const void* q, const float* q_scale, const fl
                         int j0, int j1, bool all_groups, int agg, void* pq, float* psc, float* pw, hipStream_t stream,
                         const LinOut& lo = LinOut{});
 
-// The fp8 epilogue's linear term (mfma_tile.h) for flat rows [r0, r1) of an
-// fp8 row array: lin [rows, 4 * 128] codes, lin_scale [rows, 4].  The two-set
-// form covers two row arrays (e.g. query rows and their proxies) in one launch.
-struct LinRows {
-  const uint8_t* q = nullptr;
-  const float* q_scale = nullptr;
-  const float* w = nullptr;
-  int64_t r0 = 0, r1 = 0;
-  uint8_t* lin = nullptr;
-  float* lin_scale = nullptr;
-};
-hipError_t launch_lin(const LinRows& set0, const LinRows& set1, hipStream_t stream);
-hipError_t launch_lin(const void* q, const float* q_scale, const float* w, int64_t r0, int64_t r1, uint8_t* lin,
-                      float* lin_scale, hipStream_t stream);
+// The fp8 epilogue's linear term (mfma_tile.h) for rows [0, n) of an fp8 row
+// array: lin [rows, 4 * 128] codes, lin_scale [rows, 4]; and for the leading
+// dense rows of each sequence (arrays placed as SeqTable says).
+hipError_t launch_lin(const void* q, const float* q_scale, const float* w, int64_t n, uint8_t* lin, float* lin_scale,
+                      hipStream_t stream);
+hipError_t launch_lin_dense(const void* q, const float* q_scale, const float* w, const SeqTable& st, uint8_t* lin,
+                            float* lin_scale, hipStream_t stream);
 
 // Score rows of a launch: rows rs (row data [rows, H, d] indexed by row_index(),
 // with lin / lin_scale rows in the same order for fp8) against each sequence's
@@ -75,10 +68,10 @@ hipError_t launch_score(int dtype, const ScoreRows& rows, const ScoreRows* more,
                         const KeyMap& km, const SeqTable& st, bool out_bf16, hipStream_t stream);
 
 // Top-m of score rows (fp32, or bf16 when scores_bf16): row (b, i) has
-// limit + 1 valid entries; lim_max is the largest limit.  Up to 256 long rows
-// (decode) are split over several workgroups each when `scratch` holds
-// split_scratch_bytes(rows) (else one 1024-thread workgroup each); more rows
-// take one 512-thread workgroup each.
+// limit + 1 valid entries; lim_max is the largest limit.  Rows are held in
+// registers by one workgroup each, or streamed when longer than that; up to 256
+// such long rows are split over several workgroups each when `scratch` holds
+// split_scratch_bytes(rows) (select.hip).
 hipError_t launch_topk(const void* scores, bool scores_bf16, int64_t ld, const SeqTable& st, const RowSpace& rs,
                        const OutDesc& od, int64_t lim_max, void* scratch, size_t scratch_bytes,
                        hipStream_t stream);
@@ -96,7 +89,7 @@ hipError_t launch_topk_both(bool scores_bf16, const SeqTable& st, const TopkRows
                             hipStream_t stream);
 size_t split_scratch_bytes(int64_t rows);
 constexpr int kSplitMaxRows = 256;   // launches with more rows do not split
-constexpr int kSplitMinKeys = 16384; // nor do launches whose rows are all shorter
+constexpr int kSplitMinKeys = 16384; // nor do launches whose rows are all shorter (the resident select raises this for m <= 4608)
 
 // Refine (Eqs. 8-9) for groups [j0, j1) with j >= first_proxy[b]: re-score
 // the candidate rows [groups, c] into rescore [groups, g, c] (bf16 scores

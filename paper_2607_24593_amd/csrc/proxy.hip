@@ -385,28 +385,46 @@ hipError_t launch_encode_e4m3(const float* x, uint8_t* out, int64_t n, hipStream
 
 namespace pivot {
 
-// Linear terms (lin_row) of flat row ranges, one wave per row.
-__global__ __launch_bounds__(256) void lin_kernel(LinRows set0, LinRows set1, int64_t blocks0) {
-  const bool first = blockIdx.x < blocks0;
-  const LinRows rs = first ? set0 : set1;
-  const int64_t row = rs.r0 + ((int64_t)blockIdx.x - (first ? 0 : blocks0)) * 4 + (threadIdx.x >> 6);
-  if (row >= rs.r1) return;
-  lin_row(rs.q + row * (int64_t)(kH * kD), rs.w + row * kH, rs.q_scale[row], rs.lin + row * (int64_t)kLinBytes,
-          rs.lin_scale + row * kLinLevels, threadIdx.x & 63);
+// Linear terms (lin_row) of rows [0, n), one wave per row.
+__global__ __launch_bounds__(256) void lin_kernel(const uint8_t* __restrict__ q, const float* __restrict__ q_scale,
+                                                  const float* __restrict__ w, int64_t n, uint8_t* __restrict__ lin,
+                                                  float* __restrict__ lin_scale) {
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  lin_row(q + row * (int64_t)(kH * kD), w + row * kH, q_scale[row], lin + row * (int64_t)kLinBytes,
+          lin_scale + row * kLinLevels, threadIdx.x & 63);
 }
 
-hipError_t launch_lin(const LinRows& set0, const LinRows& set1, hipStream_t stream) {
-  const int64_t b0 = set0.r1 > set0.r0 ? (set0.r1 - set0.r0 + 3) / 4 : 0;
-  const int64_t b1 = set1.r1 > set1.r0 ? (set1.r1 - set1.r0 + 3) / 4 : 0;
-  if (b0 + b1 == 0) return hipSuccess;
-  if (b0 + b1 > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(lin_kernel, dim3((unsigned)(b0 + b1)), dim3(256), 0, stream, set0, set1, b0);
+hipError_t launch_lin(const void* q, const float* q_scale, const float* w, int64_t n, uint8_t* lin, float* lin_scale,
+                      hipStream_t stream) {
+  const int64_t blocks = (n + 3) / 4;
+  if (n <= 0) return hipSuccess;
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(lin_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint8_t*)q, q_scale, w, n, lin,
+                     lin_scale);
   return hipGetLastError();
 }
 
-hipError_t launch_lin(const void* q, const float* q_scale, const float* w, int64_t r0, int64_t r1, uint8_t* lin,
-                      float* lin_scale, hipStream_t stream) {
-  return launch_lin(LinRows{(const uint8_t*)q, q_scale, w, r0, r1, lin, lin_scale}, LinRows{}, stream);
+// Linear terms of the leading dense rows (the guardrail's) of each sequence.
+__global__ __launch_bounds__(256) void lin_dense_kernel(const uint8_t* __restrict__ q,
+                                                        const float* __restrict__ q_scale,
+                                                        const float* __restrict__ w, SeqTable st,
+                                                        uint8_t* __restrict__ lin, float* __restrict__ lin_scale) {
+  const int b = blockIdx.y, i = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (b >= st.n || i >= st.dense_rows[b]) return;
+  const int64_t row = (int64_t)st.row0[b] + i;
+  lin_row(q + row * (int64_t)(kH * kD), w + row * kH, q_scale[row], lin + row * (int64_t)kLinBytes,
+          lin_scale + row * kLinLevels, threadIdx.x & 63);
+}
+
+hipError_t launch_lin_dense(const void* q, const float* q_scale, const float* w, const SeqTable& st, uint8_t* lin,
+                            float* lin_scale, hipStream_t stream) {
+  int most = 0;
+  for (int b = 0; b < st.n; ++b) most = std::max(most, st.dense_rows[b]);
+  if (most <= 0) return hipSuccess;
+  hipLaunchKernelGGL(lin_dense_kernel, dim3((unsigned)((most + 3) / 4), (unsigned)st.n), dim3(256), 0, stream,
+                     (const uint8_t*)q, q_scale, w, st, lin, lin_scale);
+  return hipGetLastError();
 }
 
 }  // namespace pivot
