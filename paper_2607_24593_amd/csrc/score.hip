@@ -347,7 +347,11 @@ static int64_t floor_sum(int64_t n, int64_t m, int64_t b, int64_t a) {
 // time idle: the estimate is the mean of the two.
 //   Keys mode (bound by loads in flight): four fp8 or two bf16 workgroups run
 // on a CU at once, each at its own pace, so a round holds 1024 or 512.
-// Less than a round takes one workgroup's time.  Counted are the (row block,
+// Less than a round takes one workgroup's time, but below 512 keys only while
+// every workgroup has a CU to itself: past that a workgroup's prologue slows
+// its neighbours.  Us a call, with the bound and without: 6 fp8 requests of 16K
+// keys, 3 dense rows each, 29.0 and 38.4; 15 fp8 rows of 1.5K-7K keys 60.3 and
+// 66.2; 8 bf16 rows of 0.7K-7K 38.3 and 43.5.  Counted are the (row block,
 // segment) pairs that hold keys.
 //   Measured, us a call (segments of 4096 / 2048 / 1024 / 512 / 256 / 128 keys;
 //   in brackets: the choice among these):
@@ -395,6 +399,7 @@ static int score_segment(const SeqTable& st, const RowSpace& rs0, const RowSpace
     int64_t wgs = 0;
     for (int u = 0; u < n_seq; ++u)
       if (seq[u].n > 0) wgs += floor_sum(seq[u].n, seg, seq[u].step, seq[u].first - 1) + seq[u].n;
+    if (keys_mode && seg < 512 && wgs > 256) break;
     const double wg = load + seg;
     const double rounds = std::ceil((double)wgs / slots) * wg;
     const double even = ((double)wgs * load + (double)all_keys) / slots + 0.5 * wg;
