@@ -867,8 +867,8 @@ struct SelectRows {
 // CAP keys, the m-th key lies past the histogram, the bin is too long) it goes
 // on with bucket_select, block_select or the two-pass select, so every row is
 // exact.
-// FILTER, for few rows (decode), whose threads hold many vectors of which few
-// reach the threshold: step 2 first lists the vectors with a key that does (a
+// FILTER, for few long rows (decode), whose threads hold many vectors of which
+// few reach the threshold: step 2 first lists the vectors with a key that does (a
 // packed maximum and one ballot per vector), and examines only those, dealt
 // evenly to the threads and read again (from L2).
 // What bounds it: the fixed phases' latency and LDS operations, not the bytes
@@ -1301,17 +1301,16 @@ static int64_t min_limit(const SeqTable& st, const RowSpace& rs) {
 constexpr int64_t kResident = 32768;
 
 // `blocks` rows of `set`, then `more_blocks` of `more`.
-template <int T, int V, class E>
+template <int T, int V, bool FILTER, class E>
 static hipError_t resident_launch(const SelectRows<E>& set, const SelectRows<E>* more, int blocks, int more_blocks,
                                   const SeqTable& st, hipStream_t stream) {
-  constexpr bool kFilter = T == kSelThreadsWide;
   const SelectRows<E>& second = more ? *more : set;
   const dim3 grid((unsigned)(blocks + more_blocks));
   if (std::max(set.od.m, second.od.m) <= kSelCapSmall / 2)
-    hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCapSmall, E, kFilter>), grid, dim3(T), 0, stream, set, second,
+    hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCapSmall, E, FILTER>), grid, dim3(T), 0, stream, set, second,
                        blocks, st);
   else
-    hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCap16, E, kFilter>), grid, dim3(T), 0, stream, set, second,
+    hipLaunchKernelGGL((topk_resident_kernel<T, V, kSelCap16, E, FILTER>), grid, dim3(T), 0, stream, set, second,
                        blocks, st);
   return hipGetLastError();
 }
@@ -1323,8 +1322,8 @@ static hipError_t resident_512(const SelectRows<E>& set, const SelectRows<E>* mo
   constexpr int V = 32 / ScoreVec<E>::N * 2;  // vectors of a thread that make kResident
   if constexpr (sizeof(E) == 4)
     if (lim_max + 1 <= kResident / 2)
-      return resident_launch<kSelThreads, V / 2, E>(set, more, blocks, more_blocks, st, stream);
-  return resident_launch<kSelThreads, V, E>(set, more, blocks, more_blocks, st, stream);
+      return resident_launch<kSelThreads, V / 2, false, E>(set, more, blocks, more_blocks, st, stream);
+  return resident_launch<kSelThreads, V, false, E>(set, more, blocks, more_blocks, st, stream);
 }
 
 bool topk_both_ok(bool, const SeqTable& st, const TopkRows& a, const TopkRows& b) {
@@ -1357,9 +1356,22 @@ static hipError_t topk_launch(const E* scores, int64_t ld, const SeqTable& st, c
   constexpr int N = ScoreVec<E>::N;
   if (od.m <= kResidentMaxM) {
     const SelectRows<E> set{scores, ld, rs, od};
-    // few rows (decode): a wide workgroup holds up to 131072 bf16 or 65536 fp32 scores
-    if (blocks <= kWideMaxRows && lim_max + 1 <= 16 * kSelThreadsWide * N)
-      return resident_launch<kSelThreadsWide, 16, E>(set, nullptr, (int)blocks, 0, st, stream);
+    // few rows (decode): a wide workgroup holds up to 131072 bf16 or 65536 fp32
+    // scores, 16 vectors a thread.  Shorter rows take a kernel of fewer: the
+    // vectors past a row's end are skipped one branch at a time, and of rows
+    // this short most vectors hold a kept key, so a list of them (FILTER) costs
+    // more than it saves.  Us a launch of one row, 16 vectors and this choice:
+    // fp32, 6000 scores 9.3 and 7.5 (m = 2048), 16384 10.4 and 9.1, 32768 12.0
+    // and 11.3; bf16 decode steps (one request, Refine) of 6001 keys 33.6 and
+    // 31.6, 24000 37.0 and 35.2, 65536 41.0 and 40.5.  200 rows gain as much.
+    if (blocks <= kWideMaxRows) {
+      constexpr int64_t W = (int64_t)kSelThreadsWide * N;  // scores of one vector a thread
+      const int64_t len = lim_max + 1;
+      if (len <= 2 * W) return resident_launch<kSelThreadsWide, 2, false, E>(set, nullptr, (int)blocks, 0, st, stream);
+      if (len <= 4 * W) return resident_launch<kSelThreadsWide, 4, false, E>(set, nullptr, (int)blocks, 0, st, stream);
+      if (len <= 8 * W) return resident_launch<kSelThreadsWide, 8, true, E>(set, nullptr, (int)blocks, 0, st, stream);
+      if (len <= 16 * W) return resident_launch<kSelThreadsWide, 16, true, E>(set, nullptr, (int)blocks, 0, st, stream);
+    }
     if (lim_max + 1 <= kResident) return resident_512<E>(set, nullptr, (int)blocks, 0, lim_max, st, stream);
     // one sequence whose rows grow past that: its shorter rows on their own
     if (st.n == 1 && rs.step > 0) {

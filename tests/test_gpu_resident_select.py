@@ -54,6 +54,7 @@ def _check(rows, n0, step, m, bf16, ld_pad=0, off=0, label=""):
     (65537, 2048, 2), (131071, 4608, 2), (131072, 2048, 2), (131073, 2048, 2),
     (2048, 2047, 260), (4101, 2048, 260), (8192, 4096, 260), (16384, 2048, 260), (16385, 4608, 260),
     (20011, 2048, 260), (32768, 4096, 260), (32769, 4096, 260),
+    (8192, 4096, 2), (16384, 4096, 2), (16385, 4608, 2), (32768, 4096, 2), (65536, 4096, 256),  # edges of few rows
 ])
 def test_lengths(n, m, R, bf16):
     rng = np.random.default_rng(n + m)
