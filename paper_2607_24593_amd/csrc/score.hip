@@ -23,13 +23,12 @@
 // active (row block, segment) pairs still spread evenly over the XCDs
 // (pinning segments to XCDs would idle the XCDs that own the late segments of
 // short prefixes).  Keys mode runs x = key segment, y = sequence.  The segment
-// length adapts to the launch (score_segment).
-#include <algorithm>
+// length adapts to the launch (segment.h).
 #include <climits>
-#include <cmath>
 
 #include "launch.h"
 #include "mfma_tile.h"
+#include "segment.h"
 
 namespace pivot {
 
@@ -319,108 +318,12 @@ __global__ __launch_bounds__(256) void score_kernel(RowArgs set0, RowArgs set1, 
   }
 }
 
-// sum over i in [0, n) of floor((a + b i) / m), a, b >= 0, m > 0.
-// One term (a decode sequence) takes one 32-bit divide: the estimate of a
-// launch of 64 such sequences takes 4.5 us of host time instead of 15.
-static int64_t floor_sum(int64_t n, int64_t m, int64_t b, int64_t a) {
-  if (n == 1 && a <= UINT32_MAX) return (uint32_t)a / (uint32_t)m;
-  int64_t s = 0;
-  while (n > 0) {
-    s += n * (n - 1) / 2 * (b / m) + n * (a / m);
-    b %= m;
-    a %= m;
-    const int64_t top = a + b * n;
-    if (top < m) break;
-    n = top / m;  // the same points counted along the other axis
-    a = top % m;
-    std::swap(m, b);
-  }
-  return s;
-}
-
-// The key segment of a launch: the length with the shortest estimated time up
-// to max_seg: in keys mode a multiple of 64 keys, in rows mode a multiple of 256
-// (the lengths between measured slower than both neighbours) or 64 or 128; with
-// paged keys a power of two of at least 128, so that a segment starts on a page
-// boundary or lies inside one page.  A
-// workgroup costs its prologue (row tile, scales, first keys: as much as scoring
-// `load` keys) and its keys.
-//   Rows mode (MFMA bound): launches of a few workgroups per CU run in rounds
-// of 256; in long ones the CUs share the sum and end with half a workgroup's
-// time idle: the estimate is the mean of the two.
-//   Keys mode (bound by loads in flight): four fp8 or two bf16 workgroups run
-// on a CU at once, each at its own pace, so a round holds 1024 or 512.
-// Less than a round takes one workgroup's time, but below 512 keys only while
-// every workgroup has a CU to itself: past that a workgroup's prologue slows
-// its neighbours.  Us a call, with the bound and without: 6 fp8 requests of 16K
-// keys, 3 dense rows each, 29.0 and 38.4; 15 fp8 rows of 1.5K-7K keys 60.3 and
-// 66.2; 8 bf16 rows of 0.7K-7K 38.3 and 43.5.  Counted are the (row block,
-// segment) pairs that hold keys.
-//   Measured, us a call (segments of 4096 / 2048 / 1024 / 512 / 256 / 128 keys;
-//   in brackets: the choice among these):
-//     fp8, five packed requests of 3K-30K keys  795 / [773] / 789 /  -  /  -  /  -
-//     fp8, 8192 queries at 128K, groups of 4  [1780] / 1812 / 1868 /  -  /  -  /  -
-//     fp8, 500 rows of 20K keys                  -  /   -  /   -  / [94] / 113 /  -
-//     bf16, 1025 rows of 24K keys (max 2048)     -  / [667] / 683 /  -  /  -  /  -
-//     bf16, 2048 queries from 0                  -  /   -  /   -  / [74] /  74 /  82
-//       (192, 320 and 384 keys: 79, 81, 78)
-//     fp8, 24 decode rows of 5K-70K keys         -  / 64 / [50.7] / 55.2 / - / -
-//     bf16, 8 decode rows of 40K keys            -  / 80 / 74.4 / 72.7 / 76.5 / 92
-//   and at 640 keys [69.5]; 500 rows of 20K keys at 1280 and 2560 keys 90, [91];
-//   fp8, 32 decode rows of 128K keys at 2048, 1536 and 1024 keys [159.6], 163, 164.5
-static int score_segment(const SeqTable& st, const RowSpace& rs0, const RowSpace* rs1, int rb, int max_seg,
-                         bool keys_mode, bool fp8, bool paged) {
-  const int load = keys_mode || fp8 ? 160 : 256;
-  const double slots = !keys_mode ? 256.0 : fp8 ? 1024.0 : 512.0;
-  struct Blocks {
-    int64_t n, first, step;  // row blocks, keys of the first one, keys more per block
-  } seq[2 * kMaxSeq];
-  int64_t all_keys = 0;
-  const int n_seq = rs1 ? 2 * st.n : st.n;
-  for (int u = 0; u < n_seq; ++u) {
-    const int b = u % st.n;
-    const RowSpace& rs = u < st.n ? rs0 : *rs1;
-    const int cnt = rs.kind == kProxyRows ? (st.n_rows[b] + rs.step - 1) / rs.step : st.n_rows[b];
-    int hi = std::min(rs.i1, cnt), lo = rs.i0;
-    if (rs.kind == kDenseRows) hi = std::min(hi, st.dense_rows[b]);
-    if (rs.kind == kProxyRows) lo = std::max(lo, st.first_proxy[b]);
-    seq[u] = Blocks{0, 0, 0};
-    if (hi <= lo) continue;
-    const int64_t b0 = (lo - rs.i0) / rb, b1 = (hi - 1 - rs.i0) / rb;
-    // a block scans the keys of its last row; the last block's last row is hi - 1
-    const int64_t end0 = std::min<int64_t>(rs.i0 + (b0 + 1) * rb, hi) - 1;
-    const int64_t k0 = st.q_pos0[b] - rs.shift + end0 * rs.step + 1, d = (int64_t)rb * rs.step;
-    const int64_t skip = k0 > 0 ? 0 : d > 0 ? (-k0) / d + 1 : b1 - b0 + 1;  // blocks with no key in reach
-    const int64_t n = std::max<int64_t>(0, b1 - b0 + 1 - skip);
-    seq[u] = Blocks{n, k0 + skip * d, d};
-    all_keys += n * seq[u].first + n * (n - 1) / 2 * d;
-  }
-  int best = max_seg;
-  double best_cost = 0.0;
-  auto shorter = [&](int seg) { return paged || (!keys_mode && seg <= 256) ? seg / 2 : seg - (keys_mode ? 64 : 256); };
-  for (int seg = max_seg; seg >= (paged ? 128 : 64); seg = shorter(seg)) {
-    int64_t wgs = 0;
-    for (int u = 0; u < n_seq; ++u)
-      if (seq[u].n > 0) wgs += floor_sum(seq[u].n, seg, seq[u].step, seq[u].first - 1) + seq[u].n;
-    if (keys_mode && seg < 512 && wgs > 256) break;
-    const double wg = load + seg;
-    const double rounds = std::ceil((double)wgs / slots) * wg;
-    const double even = ((double)wgs * load + (double)all_keys) / slots + 0.5 * wg;
-    const double cost = (double)wgs <= slots ? wg : keys_mode ? rounds : 0.5 * (rounds + even);
-    if (seg == max_seg || cost < best_cost) {
-      best = seg;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
 template <int DT, int R, bool KSPLIT, bool OB16>
 static hipError_t run_score(const ScoreRows& s, const ScoreRows* more, const void* k, const float* ks,
                             const KeyMap& km, const SeqTable& st, int max_seg, hipStream_t stream) {
   constexpr int RB = KSPLIT ? R : 4 * R;
   // <= 4096: the key scales of a segment are staged in LDS
-  const int seg = score_segment(st, s.rs, more ? &more->rs : nullptr, RB, max_seg, KSPLIT, DT == kFp8,
+  const int seg = score_segment(st, s.rs, more ? &more->rs : nullptr, RB, R, max_seg, KSPLIT, DT == kFp8,
                                 km.pages != nullptr);
   auto blocks = [&](const ScoreRows& x) { return (int64_t)st.n * ((x.rs.i1 - x.rs.i0 + RB - 1) / RB); };
   auto segs = [&](const ScoreRows& x) { return (x.lim_max + seg) / seg; };
