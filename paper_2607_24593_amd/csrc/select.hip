@@ -44,6 +44,7 @@
 
 #include "block_select.h"
 #include "launch.h"
+#include "sample.h"
 
 namespace pivot {
 
@@ -854,9 +855,9 @@ struct SelectRows {
 
 // Rows of at most T V N scores (N = 8 bf16 or 4 fp32 to a 16-byte vector): one
 // workgroup per row requests all of it at once, V vectors per thread.
-//   1 threshold  wave w's vector w mod vn (vn vectors in use) is the sample,
-//                1/vn of the row in blocks of 64 vectors spread over it
-//                (sample_base).  One vector per thread is the whole row: its
+//   1 threshold  one vector per wave and lane is the sample, 1/vn of the row
+//                (vn vectors in use), a block of 64 vectors out of every vn
+//                (sampled_vector, sample_base).  One vector per thread is the whole row: its
 //                threshold is the m-th key's bin;
 //   2 compact    the keys >= the threshold go to LDS with their positions, a
 //                ballot per score and one LDS atomic per wave and vector;
@@ -945,7 +946,7 @@ void topk_resident_kernel(SelectRows<E> set0, SelectRows<E> set1, int blocks0, S
     for (int v = 0; v < V; ++v)
       if (v < vn) a[v] = convert(a[v], v * T + tid < nv);
     // lane w: the vector that wave w samples, and the sampled vectors up to it
-    const int turn = lane % vn;
+    const int turn = sampled_vector(lane & (T / 64 - 1), T / 64, vn);
     const uint32_t sampled =
         wave_incl_sum(lane < T / 64 ? (uint32_t)max(0, min(64, nv - (turn * T + 64 * lane))) : 0u);
     const int s = N * __builtin_amdgcn_readlane((int)sampled, 63);
