@@ -830,18 +830,248 @@ struct Candidate<bf16_t, true> {
   __device__ static __forceinline__ int32_t pos(W w) { return (int32_t)(w & 0xFFFFu); }
 };
 
-// The candidates as (float key, position) pairs.
-template <int THREADS, class E, bool WORD>
-struct ResidentCands {
+// Three sums over the workgroup, in every thread.  Calls alternate between two
+// sets of words, so each needs one barrier.
+struct Three {
+  uint32_t a, b, c;
+};
+template <int T>
+__device__ __forceinline__ Three block_sums(Three x, uint32_t (&sums)[2][3][T / 64], int& turn) {
+  const int lane = threadIdx.x & 63, wave = (int)(threadIdx.x >> 6);
+  const Three s{wave_incl_sum(x.a), wave_incl_sum(x.b), wave_incl_sum(x.c)};
+  if (lane == 63) {
+    sums[turn][0][wave] = s.a;
+    sums[turn][1][wave] = s.b;
+    sums[turn][2][wave] = s.c;
+  }
+  __syncthreads();
+  // a row of 16 lanes to each sum
+  uint32_t y = lane < 48 && (lane & 15) < T / 64 ? sums[turn][lane >> 4][lane & 15] : 0u;
+  turn ^= 1;
+  y += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x111, 0xF, 0xF, true);  // row_shr:1, 2, 4, 8
+  y += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x112, 0xF, 0xF, true);
+  y += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x114, 0xF, 0xF, true);
+  y += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x118, 0xF, 0xF, true);
+  return {(uint32_t)__builtin_amdgcn_readlane((int)y, 15), (uint32_t)__builtin_amdgcn_readlane((int)y, 31),
+          (uint32_t)__builtin_amdgcn_readlane((int)y, 47)};
+}
+
+// The candidates of a row, for bisect_select and (visit) bucket_select.
+template <int T, class E, bool WORD>
+struct CandSearch {
   using C = Candidate<E, WORD>;
   const typename C::W* w;
   uint32_t base;
   int count;
+  uint32_t tied;
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+    for (int e = threadIdx.x; e < count; e += T) f(base + C::above(w[e], base), C::pos(w[e]));
+  }
   template <class F>
   __device__ __forceinline__ void visit(F f) const {
-    for (int e = threadIdx.x; e < count; e += THREADS) f(OrderKey<E>::as_float_key(base + C::above(w[e], base)), C::pos(w[e]));
+    each([&](uint32_t key, int32_t pos) { f(OrderKey<E>::as_float_key(key), pos); });
+  }
+  __device__ __forceinline__ Three at_least(uint32_t k1, uint32_t k2, uint32_t k3) const {
+    Three n{0, 0, 0};
+    each([&](uint32_t key, int32_t) {
+      n.a += (uint32_t)(key >= k1);
+      n.b += (uint32_t)(key >= k2);
+      n.c += (uint32_t)(key >= k3);
+    });
+    return n;
+  }
+  __device__ __forceinline__ void tie(uint32_t k) { tied = k; }
+  __device__ __forceinline__ Three ties_to(int p1, int p2, int p3) const {
+    Three n{0, 0, 0};
+    each([&](uint32_t key, int32_t pos) {
+      n.a += (uint32_t)(key == tied && pos <= p1);
+      n.b += (uint32_t)(key == tied && pos <= p2);
+      n.c += (uint32_t)(key == tied && pos <= p3);
+    });
+    return n;
+  }
+  __device__ __forceinline__ uint32_t take(uint32_t k, int last) {
+    uint32_t n = 0;
+    each([&](uint32_t key, int32_t pos) { n += (uint32_t)(key > k || (key == k && pos <= last)); });
+    return n;
+  }
+  template <class Put>
+  __device__ __forceinline__ void emit(uint32_t k, int last, int slot, Put put) const {
+    each([&](uint32_t key, int32_t pos) {
+      if (key > k || (key == k && pos <= last)) put(slot++, pos);
+    });
   }
 };
+
+// A row in registers, for bisect_select: V vectors of order keys per thread (vn
+// in use, the others and those past the row's end 0), from the score `head` on,
+// and one key more (tkey, of score te) in the first threads.
+template <int T, int V, class E>
+struct RowSearch {
+  using OK = OrderKey<E>;
+  static constexpr int N = ScoreVec<E>::N, WORDS = (V * N + 31) / 32;
+  uint4 a[V];
+  int vn, head;
+  uint32_t tkey;
+  int te;
+  uint32_t mask[WORDS];  // this thread's tied, then its taken scores
+  bool tmask;
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (v < vn) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) f(OK::at(a[v], j), head + N * (v * T + (int)threadIdx.x) + j);
+      }
+    f(tkey, te);
+  }
+  __device__ __forceinline__ Three at_least(uint32_t k1, uint32_t k2, uint32_t k3) const {
+    Three n{(uint32_t)(tkey >= k1), (uint32_t)(tkey >= k2), (uint32_t)(tkey >= k3)};
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (v < vn) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          n.a += (uint32_t)OK::reaches(a[v], j, k1);
+          n.b += (uint32_t)OK::reaches(a[v], j, k2);
+          n.c += (uint32_t)OK::reaches(a[v], j, k3);
+        }
+      }
+    return n;
+  }
+  template <class F>
+  __device__ __forceinline__ void mark(F f) {
+#pragma unroll
+    for (int u = 0; u < WORDS; ++u) mask[u] = 0;
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (v < vn) {
+        const int p0 = head + N * (v * T + (int)threadIdx.x);
+#pragma unroll
+        for (int j = 0; j < N; ++j) mask[(v * N + j) / 32] |= (uint32_t)f(OK::at(a[v], j), p0 + j) << ((v * N + j) % 32);
+      }
+    tmask = f(tkey, te);
+  }
+  __device__ __forceinline__ void tie(uint32_t k) {
+    mark([&](uint32_t key, int) { return key == k; });
+  }
+  // ties at most at position `last`: a prefix of the mask
+  __device__ __forceinline__ uint32_t ties_to(int last) const {
+    const int x = last - head - N * (int)threadIdx.x;
+    const int upto = x < 0 ? 0 : N * (x / (N * T)) + min(N, x % (N * T) + 1);
+    uint32_t n = (uint32_t)(tmask && te <= last);
+#pragma unroll
+    for (int u = 0; u < WORDS; ++u) {
+      const int bits = min(max(upto - 32 * u, 0), 32);
+      n += (uint32_t)__popc(mask[u] & (uint32_t)((1ull << bits) - 1ull));
+    }
+    return n;
+  }
+  __device__ __forceinline__ Three ties_to(int p1, int p2, int p3) const {
+    return {ties_to(p1), ties_to(p2), ties_to(p3)};
+  }
+  __device__ __forceinline__ uint32_t take(uint32_t k, int last) {
+    mark([&](uint32_t key, int pos) { return key > k || (key == k && pos <= last); });
+    uint32_t n = (uint32_t)tmask;
+#pragma unroll
+    for (int u = 0; u < WORDS; ++u) n += (uint32_t)__popc(mask[u]);
+    return n;
+  }
+  template <class Put>
+  __device__ __forceinline__ void emit(uint32_t, int, int slot, Put put) const {
+#pragma unroll
+    for (int u = 0; u < WORDS; ++u)
+      for (uint32_t x = mask[u]; x != 0; x &= x - 1) {
+        const int at = 32 * u + __ffs((int)x) - 1;
+        put(slot++, head + N * (at / N * T + (int)threadIdx.x) + at % N);
+      }
+    if (tmask) put(slot, te);
+  }
+};
+
+// Exact top-m of a source whose keys are counted, not sorted: cuts the range
+// [lo, hi] of the m-th largest key in four by three counts at a time, then,
+// among keys equal to it, the range of the last position taken.  At the start
+// c_lo keys are >= lo (at least m), c_hi above hi (fewer than m); n bounds the
+// positions.  The first cuts narrow the range to keys that occur and try its
+// ends, which decides at once where many keys are equal.  At most 3 + 16 cuts
+// for the key and 9 for the position, each a few instructions per key and a
+// barrier or two: its time hardly depends on how the keys are distributed, where
+// histograms of equal keys serialise on one LDS word.
+template <int T, class Src, class Put>
+__device__ __forceinline__ void bisect_select(Src& src, uint32_t lo, uint32_t c_lo, uint32_t hi, uint32_t c_hi,
+                                              uint32_t m, int n, uint32_t (&sums)[2][3][T / 64], SelectShared& sh,
+                                              Put put) {
+  int turn = 0;
+  for (int cut = 0; lo < hi && c_lo != m; ++cut) {
+    uint32_t k1, k2, k3;  // lo < k1 <= k2 <= k3 <= hi
+    if (cut < 3) {
+      uint32_t kmin = ~0u, kmax = 0u;
+      src.each([&](uint32_t key, int32_t) {
+        if (key >= lo) kmin = min(kmin, key);
+        if (key <= hi) kmax = max(kmax, key);
+      });
+      block_pair_reduce<T, true>(kmin, kmax, sh);
+      lo = kmin;
+      hi = kmax;
+      if (lo == hi) break;
+      k1 = lo + 1;
+      k2 = lo + (hi - lo + 1) / 2;
+      k3 = hi;
+    } else {
+      const uint32_t range = hi - lo;
+      k1 = lo + (range >> 2) + 1;
+      k2 = lo + (range >> 1) + 1;
+      k3 = hi - (range >> 2);
+    }
+    const Three c = block_sums<T>(src.at_least(k1, k2, k3), sums, turn);
+    if (c.c >= m) {
+      lo = k3;
+      c_lo = c.c;
+    } else if (c.b >= m) {
+      lo = k2;
+      c_lo = c.b;
+      hi = k3 - 1;
+      c_hi = c.c;
+    } else if (c.a >= m) {
+      lo = k1;
+      c_lo = c.a;
+      hi = k2 - 1;
+      c_hi = c.b;
+    } else {
+      hi = k1 - 1;
+      c_hi = c.a;
+    }
+  }
+  int last = n;
+  if (c_lo != m) {  // more keys equal the m-th than are taken: those of the lowest positions
+    const uint32_t rem = m - c_hi;
+    src.tie(lo);
+    int p0 = 0, p1 = n - 1;  // the rem-th tie lies in [p0, p1]
+    while (p0 < p1) {
+      const int range = p1 - p0, q1 = p0 + (range >> 2), q2 = p0 + (range >> 1), q3 = p1 - 1 - (range >> 2);
+      const Three c = block_sums<T>(src.ties_to(q1, q2, q3), sums, turn);
+      if (c.a >= rem) {
+        p1 = q1;
+      } else if (c.b >= rem) {
+        p0 = q1 + 1;
+        p1 = q2;
+      } else if (c.c >= rem) {
+        p0 = q2 + 1;
+        p1 = q3;
+      } else {
+        p0 = q3 + 1;
+      }
+    }
+    last = p0;
+  }
+  const uint32_t mine = src.take(lo, last), sum = wave_incl_sum(mine);
+  int slot = 0;
+  if ((threadIdx.x & 63) == 63) slot = atomicAdd(&sh.emitted, (int)sum);
+  src.emit(lo, last, __builtin_amdgcn_readlane(slot, 63) + (int)(sum - mine), put);
+}
 
 // A set of rows of a resident select launch; blocks [0, blocks0) take the
 // first, the others the second (the proxies' rows and the guardrail's).
@@ -857,17 +1087,17 @@ struct SelectRows {
 // workgroup per row requests all of it at once, V vectors per thread.
 //   1 threshold  one vector per wave and lane is the sample, 1/vn of the row
 //                (vn vectors in use), a block of 64 vectors out of every vn
-//                (sampled_vector, sample_base).  One vector per thread is the whole row: its
-//                threshold is the m-th key's bin;
+//                (sampled_vector, sample_base).  One vector per thread is the
+//                whole row: its threshold is the m-th key's bin;
 //   2 compact    the keys >= the threshold go to LDS with their positions, a
 //                ballot per score and one LDS atomic per wave and vector;
 //   3 select     a histogram of their distance above the threshold gives the
 //                bin with the m-th key; every candidate above it is taken, and
 //                its members are ranked by (key, position).
-// Outside those rules (the sample's threshold kept fewer than m or more than
-// CAP keys, the m-th key lies past the histogram, the bin is too long) it goes
-// on with bucket_select, block_select or the two-pass select, so every row is
-// exact.
+// Outside those rules the select goes on with bucket_select (the m-th key lies
+// past the histogram) or bisect_select: over the candidates where the bin is too
+// long, over the row, loaded again, where the threshold kept fewer than m or
+// more than CAP keys.  So every row is exact.
 // FILTER, for few long rows (decode), whose threads hold many vectors of which
 // few reach the threshold: step 2 first lists the vectors with a key that does (a
 // packed maximum and one ballot per vector), and examines only those, dealt
@@ -890,12 +1120,11 @@ void topk_resident_kernel(SelectRows<E> set0, SelectRows<E> set1, int blocks0, S
   using C = Candidate<E, WORD>;
   constexpr int CAND_BYTES = ((int)sizeof(typename C::W) * (CAP + 1) + 15) / 16 * 16;  // one slot takes the overflow
   constexpr int LDS = CAND_BYTES + 4 * kNB16;
-  constexpr int CAP2 = ((LDS - (int)sizeof(TwoLevelShared<0>)) / 8) / 64 * 64;
   static_assert(CAND_BYTES >= 4 * 4096, "the sampling histogram lies within the candidates");
-  static_assert(CAP2 > 0 && (int)sizeof(TwoLevelShared<CAP2>) <= LDS, "fallback fits the region");
   __shared__ __attribute__((aligned(16))) uint8_t raw[LDS];
   __shared__ uint16_t vlist[FILTER ? T * V : 1];  // vectors with a key that reaches the threshold
   __shared__ SelectShared sel;
+  __shared__ uint32_t sums[2][3][T / 64];
   __shared__ int32_t lcount, kept, listed;
   const bool second = (int)blockIdx.x >= blocks0;
   const E* const scores = second ? set1.scores : set0.scores;
@@ -928,23 +1157,29 @@ void topk_resident_kernel(SelectRows<E> set0, SelectRows<E> set1, int blocks0, S
     kept = 0;
     listed = 0;
   }
-  if (vn >= 1 && vn <= V) {
-    uint4 a[V];
+  // the scores before the first vector and after the last: one each for the first threads
+  const int te = tid < head ? tid : tid + N * nv;
+  const uint32_t tkey = te < n && tid < 2 * N ? OK::one(row[te]) : 0u;
+  auto convert = [](uint4 x, bool in) {
+    return make_uint4(in ? OK::convert(x.x) : 0u, in ? OK::convert(x.y) : 0u, in ? OK::convert(x.z) : 0u,
+                      in ? OK::convert(x.w) : 0u);
+  };
+  auto load_row = [&](uint4 (&a)[V]) {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       a[v] = make_uint4(0u, 0u, 0u, 0u);
       if (v < vn && v * T + tid < nv) a[v] = r16[v * T + tid];
     }
-    // the scores before the first vector and after the last: one each for the first threads
-    const int te = tid < head ? tid : tid + N * nv;
-    const uint32_t tkey = te < n && tid < 2 * N ? OK::one(row[te]) : 0u;
-    auto convert = [](uint4 x, bool in) {
-      return make_uint4(in ? OK::convert(x.x) : 0u, in ? OK::convert(x.y) : 0u, in ? OK::convert(x.z) : 0u,
-                        in ? OK::convert(x.w) : 0u);
-    };
 #pragma unroll
     for (int v = 0; v < V; ++v)
       if (v < vn) a[v] = convert(a[v], v * T + tid < nv);
+  };
+  // what the threshold leaves to bisect_select over the row: c_lo keys >= lo, c_hi above hi
+  constexpr uint32_t kTop = sizeof(E) == 2 ? 0xFFFFu : ~0u;
+  uint32_t lo = 1, c_lo = (uint32_t)n, hi = kTop, c_hi = 0;
+  if (vn >= 1) {
+    uint4 a[V];
+    load_row(a);
     // lane w: the vector that wave w samples, and the sampled vectors up to it
     const int turn = sampled_vector(lane & (T / 64 - 1), T / 64, vn);
     const uint32_t sampled =
@@ -1051,8 +1286,7 @@ void topk_resident_kernel(SelectRows<E> set0, SelectRows<E> set1, int blocks0, S
         __syncthreads();
         find_digit<T, true, kNB16>(hist, sel, (uint32_t)m);
         const uint32_t bsel = sel.digit, rem = (uint32_t)m - sel.before, in_b = sel.equal;
-        constexpr uint32_t kList = sizeof(E) == 2 ? (uint32_t)kNB16 : (uint32_t)kBucketList;
-        if (bsel != (uint32_t)(kNB16 - 1) && in_b <= kList) {
+        if (bsel != (uint32_t)(kNB16 - 1) && in_b <= (uint32_t)kBucketList) {
           uint32_t* lkey = hist;  // free once the bin is known
           int32_t* lpos = reinterpret_cast<int32_t*>(hist) + (sizeof(E) == 2 ? 0 : kBucketList);
           if (tid == 0) lcount = 0;
@@ -1086,19 +1320,39 @@ void topk_resident_kernel(SelectRows<E> set0, SelectRows<E> set1, int blocks0, S
             rank_listed<T>(in_b, rem, lkey, lpos, sel, put);
           return;
         }
-        const ResidentCands<T, E, WORD> src{cand, base, found};
-        if (!bucket_select<T, kNB16>(src, (uint32_t)m, hist, hist, reinterpret_cast<int32_t*>(hist + kBucketList),
-                                     &lcount, sel, put))
-          block_select<T, false>(src, (uint32_t)m, sel, put);
+        CandSearch<T, E, WORD> src{cand, base, found, 0u};
+        if (bsel == (uint32_t)(kNB16 - 1)) {  // past the histogram: one over the candidates' values
+          const uint32_t before = sel.before;
+          __syncthreads();
+          if (bucket_select<T, kNB16>(src, (uint32_t)m, hist, hist, reinterpret_cast<int32_t*>(hist + kBucketList),
+                                      &lcount, sel, put))
+            return;
+          bisect_select<T>(src, base + (bsel << OK::kShift), before + in_b, kTop, before, (uint32_t)m, n, sums, sel,
+                           put);
+          return;
+        }
+        const uint32_t first = base + (bsel << OK::kShift), past = (1u << OK::kShift) - 1u;
+        const uint32_t top = kTop - first < past ? kTop : first + past;
+        bisect_select<T>(src, first, sel.before + in_b, top, sel.before, (uint32_t)m, n, sums, sel, put);
         return;
+      }
+      if (found < m) {
+        hi = base - 1;
+        c_hi = (uint32_t)found;
+      } else {
+        lo = base;
+        c_lo = (uint32_t)found;
       }
     }
   }
-  TwoLevelShared<CAP2>& fb = *reinterpret_cast<TwoLevelShared<CAP2>*>(raw);
-  __syncthreads();  // the region's previous use has ended in every wave
-  if (tid == 0) fb.sel.emitted = 0;
-  RowSource<T, 4, E> src{row, n};
-  two_level_select<T>(src, (uint32_t)m, fb, put);
+  RowSearch<T, V, E> src;
+  load_row(src.a);
+  src.vn = vn;
+  src.head = head;
+  src.tkey = tkey;
+  src.te = te;
+  __syncthreads();  // sel.emitted is set
+  bisect_select<T>(src, lo, c_lo, hi, c_hi, (uint32_t)m, n, sums, sel, put);
 }
 
 // Split select, step 1: workgroup r writes row r's threshold score to
