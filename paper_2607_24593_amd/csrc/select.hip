@@ -716,7 +716,19 @@ void topk_rows16_kernel(const bf16_t* __restrict__ scores, int64_t ld, SeqTable 
   if (n >= kSampleMinLen && aligned &&
       sample_threshold16<T, CAP, CAP == kSelCapSmall ? 64 : 32>(row, n, m, reinterpret_cast<uint32_t*>(raw), sel,
                                                                fthr, base16)) {
-    const int found = stream_compact16<T, U, CAP>(row, n, fthr, base16, ckey, cpos, hist, wcnt);
+    int found;
+#pragma unroll 1
+    for (;;) {
+      found = stream_compact16<T, U, CAP>(row, n, fthr, base16, ckey, cpos, hist, wcnt);
+      if (found >= m || (base16 & 15u) == 0) break;
+      // where many scores are equal, those of the threshold's bin may all lie at
+      // its lower edge
+      base16 &= ~15u;
+      fthr = key_float(key16_expand(base16));
+      __syncthreads();
+      for (int k = tid; k < kNB16; k += T) hist[k] = 0;
+      __syncthreads();
+    }
     if (found >= m && found <= CAP) {
       const SegSource16<T, T / 64, CAP / (T / 64)> cand(ckey, cpos, wcnt);
       if (select16<T>(cand, base16, (uint32_t)m, hist, reinterpret_cast<int32_t*>(hist), &lcount, sel, put))
