@@ -1110,10 +1110,10 @@ struct SelectRows {
 // past the histogram) or bisect_select: over the candidates where the bin is too
 // long, over the row, loaded again, where the threshold kept fewer than m or
 // more than CAP keys.  So every row is exact.
-// FILTER, for few long rows (decode), whose threads hold many vectors of which
-// few reach the threshold: step 2 first lists the vectors with a key that does (a
-// packed maximum and one ballot per vector), and examines only those, dealt
-// evenly to the threads and read again (from L2).
+// FILTER, for long rows in decode or with a small m, whose threads hold many
+// vectors of which few reach the threshold: step 2 first lists the vectors with
+// a key that does (a packed maximum and one ballot per vector), and examines
+// only those, dealt evenly to the threads and read again (from L2).
 // What bounds it: the fixed phases' latency and LDS operations, not the bytes
 // (a row is a few tens of KiB per CU), so a candidate is one LDS word, and the
 // histogram is built from the candidates rather than score by score; rows of
@@ -1582,11 +1582,22 @@ static hipError_t resident_launch(const SelectRows<E>& set, const SelectRows<E>*
   return hipGetLastError();
 }
 
-// Rows of at most kResident scores.
+// Rows of at most kResident scores.  Of long ones few vectors hold a kept key
+// when m is small: FILTER.  Us a launch of rows of 32768 without and with it:
+// 600 bf16 rows, m = 100, 18.6 and 15.3 (the streaming kernel 16.7), m = 1024,
+// 22.4 and 19.8, m = 2048, 24.5 and 23.8; 3000 of 24001, m = 1024, 53.5 and
+// 53.5, m = 2048, 59 and 63; 600 fp32 rows, m = 100, 29.1 and 26.3 (26.4),
+// m = 512, 30.7 and 29.2, m = 2048, 34.6 and 38.3.
 template <class E>
 static hipError_t resident_512(const SelectRows<E>& set, const SelectRows<E>* more, int blocks, int more_blocks,
                                int64_t lim_max, const SeqTable& st, hipStream_t stream) {
   constexpr int V = 32 / ScoreVec<E>::N * 2;  // vectors of a thread that make kResident
+  const SelectRows<E>& second = more ? *more : set;
+  if (lim_max + 1 > kResident / 2 && std::max(set.od.m, second.od.m) <= (sizeof(E) == 2 ? 1024 : 512)) {
+    hipLaunchKernelGGL((topk_resident_kernel<kSelThreads, V, kSelCapSmall, E, true>),
+                       dim3((unsigned)(blocks + more_blocks)), dim3(kSelThreads), 0, stream, set, second, blocks, st);
+    return hipGetLastError();
+  }
   if constexpr (sizeof(E) == 4)
     if (lim_max + 1 <= kResident / 2)
       return resident_launch<kSelThreads, V / 2, false, E>(set, more, blocks, more_blocks, st, stream);
