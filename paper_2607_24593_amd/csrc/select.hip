@@ -3,8 +3,8 @@
 // on), for the TopK of Sec. 3.1 and of Eqs. 6-7, one workgroup per row:
 //   rows of at most 32768 scores (131072 bf16 or 65536 fp32 ones when a launch
 //     has at most 256 rows, as in decode): topk_resident_kernel, the whole row
-//     in registers;
-//   longer rows: 512 threads streaming the row (topk_rows16_kernel for bf16,
+//     in registers (but for two shapes of fp32 launches, topk_launch);
+//   other rows: 512 threads streaming the row (topk_rows16_kernel for bf16,
 //     topk_rows_kernel), or, for a launch of at most 256 rows given scratch,
 //     the split select described below.
 //
@@ -1632,7 +1632,19 @@ static hipError_t topk_launch(const E* scores, int64_t ld, const SeqTable& st, c
   const int64_t blocks = (int64_t)st.n * nrows;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   constexpr int N = ScoreVec<E>::N;
-  if (od.m <= kResidentMaxM) {
+  // fp32 rows of which half and more are wanted: their candidates leave two
+  // resident workgroups to a CU, and the two-pass select, which keeps only the
+  // boundary bin's, takes less (m = 4096, us a launch, resident and two-pass: 600
+  // rows of 6000 scores 24.6 and 20.7, 3000 of 8192 82 and 73, of 10240 87 and 90).
+  const bool mostly = sizeof(E) == 4 && blocks > kWideMaxRows && od.m > kSelCapSmall / 2 && lim_max + 1 <= 2 * od.m;
+  // fp32 rows past 16384 scores leave two resident workgroups to a CU, the
+  // streaming kernel three: for 513 to 768 rows two rounds against one (m = 2048,
+  // 600 rows of 32768 34.6 and 30.9, 768 37.0 and 34.0, 512 25.6 and 25.5, 900
+  // 41.1 and 44.9).
+  const bool one_round = sizeof(E) == 4 && blocks > 2 * 256 && blocks <= 3 * 256 && od.m <= kSelCapSmall / 2 &&
+                         lim_max + 1 > kResident / 2 && ld % N == 0 && reinterpret_cast<uintptr_t>(scores) % 16 == 0 &&
+                         min_limit(st, rs) + 1 >= kSampleMinLen;
+  if (od.m <= kResidentMaxM && !mostly && !one_round) {
     const SelectRows<E> set{scores, ld, rs, od};
     // few rows (decode): a wide workgroup holds up to 131072 bf16 or 65536 fp32
     // scores, 16 vectors a thread.  Shorter rows take a kernel of fewer: the

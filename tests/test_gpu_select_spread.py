@@ -40,6 +40,7 @@ def _shape(kind, x):
     (3, 4500, 4096), (3, 12000, 2048), (3, 50000, 2048), (2, 131072, 4608),  # 2, 4, 8, 16 vectors, 1024 threads
     (300, 2100, 2048), (300, 16384, 2048), (300, 32768, 4608),               # 8 and 16 vectors, 512 threads
     (300, 32768, 32), (300, 9000, 100), (270, 16386, 512), (270, 20011, 1024),  # listed vectors and not
+    (257, 8192, 4096), (513, 16388, 2048),                                   # fp32: two-pass, streamed
     (257, 33000, 2048),                                                      # streamed
 ])
 def test_sets(R, n, m, kind, bf16):
