@@ -16,6 +16,11 @@ constexpr int prologue_keys(bool keys_mode, bool fp8, int rows_per_wave) {
   return !keys_mode ? 224 : (fp8 ? 150 : 300) * rows_per_wave;
 }
 
+// An idle workgroup's place in the grid, in the same unit (a decode call of 64
+// sequences, 20 rows each, of which three have dense rows: 223 us without this
+// term, whose dense launch took segments of 64, 184 with it).
+constexpr double kIdleKeys = 15.0;
+
 // Blocks above which a launch's workgroups are estimated instead of counted.
 constexpr int kCountedBlocks = 256;
 
@@ -89,18 +94,22 @@ inline int score_segment(const SeqTable& st, const RowSpace& rs0, const RowSpace
   };
   for (int seg = max_seg; seg >= (paged || keys_mode ? 128 : 64); seg = shorter(seg)) {
     const double per = 1.0 / seg;
+    // rows mode: a last segment of a few keys takes next to nothing
+    const int64_t least = keys_mode ? 0 : seg / 16;
     double wgs = total * per + 0.5 * (double)n_blocks;
     if (counted) {  // (x - 0.5) / seg lies at least 0.5 / seg from a whole number: exact
       int sum = 0;
-      for (int64_t i = 0; i < n_blocks; ++i) sum += (int)((keys[i] - 0.5) * per);
+      for (int64_t i = 0; i < n_blocks; ++i) sum += (int)(std::max(0.0, keys[i] - 0.5 - (double)least) * per);
       wgs = (double)(sum + n_blocks);
     }
-    const int64_t grid = grid_rows[0] * ((grid_keys[0] + seg - 1) / seg) + grid_rows[1] * ((grid_keys[1] + seg - 1) / seg);
+    auto segs = [&](int64_t n) { return n > 0 ? (std::max<int64_t>(n - least, 1) + seg - 1) / seg : 0; };
+    const int64_t grid = grid_rows[0] * segs(grid_keys[0]) + grid_rows[1] * segs(grid_keys[1]);
     const double wg = load + std::min((double)seg, longest);
     double cost = wg;
     if (wgs > 256.0 || grid > (keys_mode ? 256 : 264)) {  // (rows mode: the last few rarely meet a long one)
       const double rounds = std::max(2.0, std::ceil(wgs / 256.0)) * (load + total / std::max(wgs, 1.0));
-      cost = 0.5 * (rounds + (wgs * load + total) / 256.0 + (keys_mode ? 0.75 : 0.5) * wg);
+      cost = 0.5 * (rounds + (wgs * load + total) / 256.0 + (keys_mode ? 0.75 : 0.5) * wg) +
+             kIdleKeys / 256.0 * std::max(0.0, (double)grid - wgs);
     }
     if (seg == max_seg || cost < best_cost) {
       best = seg;
