@@ -1027,27 +1027,35 @@ hipError_t launch_short(const E* rescore, const int32_t* cand, int g, const SeqT
 #define PIVOT_SHORT(V, T)                                                                                         \
   hipLaunchKernelGGL((topk_short_kernel<V, E, T>), sgrid, dim3(T), 0, stream, rescore, cand, g, st, j0, nj, c, rule, \
                      m, out_idx)
-  if (c <= 1024)
+#define PIVOT_MEMBER16(V, T)                                                                                     \
+  hipLaunchKernelGGL((topk_member16_kernel<V, T>), sgrid, dim3(T), 0, stream, rescore, cand, g, st, j0, nj, c, rule, \
+                     m, out_idx)
+  if (c <= 1024) {
     PIVOT_SHORT(4, 256);
-  else if (few && c <= 4096 && sizeof(E) == 2)
-    hipLaunchKernelGGL((topk_member16_kernel<4, 1024>), sgrid, dim3(1024), 0, stream,
-                       reinterpret_cast<const uint16_t*>(rescore), cand, g, st, j0, nj, c, rule, m, out_idx);
-  else if (few && sizeof(E) == 2)  // c = 4096 plus a window union, or a larger budget
-    hipLaunchKernelGGL((topk_member16_kernel<8, 1024>), sgrid, dim3(1024), 0, stream,
-                       reinterpret_cast<const uint16_t*>(rescore), cand, g, st, j0, nj, c, rule, m, out_idx);
-  else if (few && c <= 4096)
-    PIVOT_SHORT(4, 1024);
-  else if (few)
-    PIVOT_SHORT(8, 1024);
-  else if (c <= 4096 && sizeof(E) == 2)
-    hipLaunchKernelGGL((topk_member16_kernel<16, 256>), sgrid, dim3(256), 0, stream,
-                       reinterpret_cast<const uint16_t*>(rescore), cand, g, st, j0, nj, c, rule, m, out_idx);
-  else if (c <= 4096)
-    PIVOT_SHORT(16, 256);
-  else if (c <= 5120)  // c = 4096 plus a window union
-    PIVOT_SHORT(20, 256);
-  else
-    PIVOT_SHORT(32, 256);
+  } else if constexpr (sizeof(E) == 2) {
+    if (few && c <= 4096)
+      PIVOT_MEMBER16(4, 1024);
+    else if (few)  // c = 4096 plus a window union, or a larger budget
+      PIVOT_MEMBER16(8, 1024);
+    else if (c <= 4096)
+      PIVOT_MEMBER16(16, 256);
+    else if (c <= 5120)  // c = 4096 plus a window union
+      PIVOT_SHORT(20, 256);
+    else
+      PIVOT_SHORT(32, 256);
+  } else {
+    if (few && c <= 4096)
+      PIVOT_SHORT(4, 1024);
+    else if (few)
+      PIVOT_SHORT(8, 1024);
+    else if (c <= 4096)
+      PIVOT_SHORT(16, 256);
+    else if (c <= 5120)
+      PIVOT_SHORT(20, 256);
+    else
+      PIVOT_SHORT(32, 256);
+  }
+#undef PIVOT_MEMBER16
 #undef PIVOT_SHORT
   return hipGetLastError();
 }
