@@ -716,16 +716,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(V <= 16 ? 8 :
   }
 }
 
-// The member select of bf16 score rows of at most 4096 slots, 16 per thread
-// of 256: bucket_select's algorithm (the same NB value buckets over the
-// usable slots' range, so the same decisions), with the scores kept as bf16
-// pairs in registers (widened exactly on use) rather than as order keys.
-// The range, the histogram and the emission form no keys; only the boundary
-// bucket's few members get one.  Unusable slots (past the row, or excluded
-// by the window rule) are masked: their histogram count goes to a sink bin.
-// Each compare's bit mask gives the emission with one LDS atomic per wave.
-// Returns false, having emitted nothing, where bucket_select would (equal
-// values, a boundary bucket longer than kBucketList).  hist: NB + 1 LDS words.
+// The member select of bf16 score rows, V slots to each of T threads:
+// bucket_select's algorithm, with the scores kept as bf16 pairs in registers
+// (widened exactly on use) rather than as order keys.  The range, the histogram
+// and the emission form no keys; only the boundary bucket's few members get one.
+// Unusable slots (past the row, or excluded by the window rule) are masked:
+// their histogram count goes to a sink bin.  Each compare's bit mask gives the
+// emission with one LDS atomic per wave.
+//   The NB value buckets span the usable slots' range or, with 16 slots and
+// more to a thread, the bulk of it (below); the end buckets then take what lies
+// outside.  Returns false, having emitted nothing, where no range is left (equal
+// values, infinities, or a bulk of equal values) and where the boundary bucket
+// is longer than kBucketList; an end bucket can be where the m-th score lies in
+// a tail of more than kBucketList scores.  hist: NB + 1 LDS words.
 template <int V, int T, int NB>
 __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], const int32_t (&pv)[V], uint32_t vmask,
                                                 bool full, uint32_t m, uint32_t* hist, int32_t* lcount,
@@ -850,9 +853,10 @@ __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], con
   return true;
 }
 
-// Member selects of bf16 score rows with |C| <= V x T (4096: the prefill
-// Refine shape, 16 per thread of 256; MTP decode, 4 per thread of 1024): the
-// workgroup mapping, slot rules and early exits of topk_short_kernel, then
+// Member selects of bf16 score rows with |C| <= V x T (up to 4096 slots: 16 per
+// thread of 256 in prefill, 4 per thread of 1024 where few rows leave the GPU
+// empty, as in MTP decode; there up to 8192: 8 per thread): the workgroup
+// mapping, slot rules and early exits of topk_short_kernel, then
 // member_select16, falling back to block_select.
 template <int V, int T>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void topk_member16_kernel(
