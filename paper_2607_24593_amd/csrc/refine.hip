@@ -725,10 +725,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(V <= 16 ? 8 :
 // emission with one LDS atomic per wave.
 //   The NB value buckets span the usable slots' range or, with 16 slots and
 // more to a thread, the bulk of it (below); the end buckets then take what lies
-// outside.  Returns false, having emitted nothing, where no range is left (equal
-// values, infinities, or a bulk of equal values) and where the boundary bucket
-// is longer than kBucketList; an end bucket can be where the m-th score lies in
-// a tail of more than kBucketList scores.  hist: NB + 1 LDS words.
+// outside, and where the m-th score lies in the upper one's tail they are dealt
+// again over that.  Returns false, having emitted nothing, where no range is
+// left (equal values, infinities, or a bulk of equal values) and where the
+// boundary bucket is longer than kBucketList.  hist: NB + 1 LDS words.
+constexpr uint32_t kTailList = 32;  // members of the end bucket that are ranked as they are
 template <int V, int T, int NB>
 __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], const int32_t (&pv)[V], uint32_t vmask,
                                                 bool full, uint32_t m, uint32_t* hist, int32_t* lcount,
@@ -794,6 +795,27 @@ __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], con
   }
   __syncthreads();
   find_digit<T, true, NB>(hist, sh, m);
+  float f0 = fmin, s0 = scale;
+  if constexpr (V >= 16) {
+    // the m-th score lies in the upper tail that the range left out, and there
+    // are many: buckets over that tail (bucket 0: everything below, not counted)
+    const float top = key_float(kmax), edge = fmax - 1.0f / scale, width = (top - edge) / (float)(NB - 4);
+    if (sh.digit == (uint32_t)(NB - 1) && sh.equal > kTailList && fmax < top && width > 0.0f &&
+        width < __builtin_inff()) {
+      f0 = edge - 2.0f * width;
+      s0 = 1.0f / width;
+      __syncthreads();
+      for (int k = tid; k < NB; k += T) hist[k] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const int k = bucket(fv(v), f0, s0);
+        if (usable(v) && k > 0) atomicAdd(&hist[k], 1u);
+      }
+      __syncthreads();
+      find_digit<T, true, NB>(hist, sh, m);
+    }
+  }
   const int bsel = (int)sh.digit;
   const uint32_t rem = m - sh.before, in_b = sh.equal;
   __syncthreads();  // the histogram's words become the boundary list
@@ -801,10 +823,10 @@ __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], con
   uint32_t* lkey = hist;
   int32_t* lpos = reinterpret_cast<int32_t*>(hist + kBucketList);
   // The buckets are computed again rather than kept from the histogram pass
-  // (sixteen more live registers would cost occupancy); copies of fmin and
-  // scale that the compiler cannot see through keep it from reusing them.
-  const float fmin2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(fmin)));
-  const float scale2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(scale)));
+  // (sixteen more live registers would cost occupancy); copies of f0 and s0
+  // that the compiler cannot see through keep it from reusing them.
+  const float fmin2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(f0)));
+  const float scale2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s0)));
   uint32_t tb = 0, lb = 0;  // taken (bucket above bsel) and listed (bucket bsel) slots
 #pragma unroll
   for (int v = 0; v < V; ++v) {
