@@ -10,6 +10,7 @@ import oracle
 import paper_2607_24593_amd as pv
 from gpu_util import dev, host, say
 from parity import check_pivot
+from test_gpu_layout import _groups, check_batch, run_batch
 from workload.gen import make_prefill
 
 pytestmark = pytest.mark.gpu
@@ -157,9 +158,19 @@ def test_score_rows_borrow_idle_workspace(short_rows):
         assert bool((buf[less:] == 0x5A).all()), kind
 
 
+def _score_launches(call):
+    pv.pivot_profile_begin(["score"])
+    try:
+        out = call()
+    finally:
+        prof = pv.pivot_profile_end()
+    return out, prof["score"][0]
+
+
 @pytest.mark.parametrize("fmt,p0,n_q,g,c,topk,window", [
     ("fp8", 0, 6001, 4, 2048, 500, 0),     # guardrail rows and proxies in one scoring and one select launch
     ("fp8", 0, 7000, 8, 4096, 2048, 4),    # the shared window's shifted limits beside unshifted ones
+    ("fp8", 0, 6001, 2, 900, 200, 0),      # member scores smaller than the score tiles
     ("bf16", 0, 2047, 3, 512, 200, 0),     # 171 guardrail groups, the last one cut by the threshold
     ("bf16", 900, 1200, 2, 1024, 300, 3),  # 124 dense rows
     ("fp8", 500, 560, 4, 520, 100, 0),     # 20 dense rows
@@ -168,8 +179,10 @@ def test_score_rows_borrow_idle_workspace(short_rows):
 @pytest.mark.parametrize("mode", ["reuse", "refine"])
 def test_guardrail_beside_proxies(inputs, fmt, p0, n_q, g, c, topk, window, mode):
     """Calls with groups on both sides of the guardrail against the oracle (the
-    sampled groups include both sides of it), and the same sets when the
-    workspace has no room for both score tiles at once."""
+    sampled groups include both sides of it), and the same sets with the least
+    workspace, in which the two sets of score rows are apart unless the idle
+    regions (Refine's member scores) hold them together; the count of scoring
+    launches says which."""
     if window and mode == "reuse":
         pytest.skip("the window applies to Refine")
     x, n_k, ng = inputs[fmt], p0 + n_q, -(-n_q // g)
@@ -179,19 +192,45 @@ def test_guardrail_beside_proxies(inputs, fmt, p0, n_q, g, c, topk, window, mode
     args = (dev(x.q[p0:n_k]), dev(qs), dev(x.w[p0:n_k]), dev(x.k[:n_k]), dev(ks), p0, n_k, topk)
     m = pv.PIVOT_REFINE if mode == "refine" else pv.PIVOT_REUSE
     cand = torch.full((1, ng, c), -7, dtype=torch.int32, device="cuda") if mode == "refine" else None
-    got = host(pv.pivot_group_index_opts(*args, m, g, c, window=window, out_cand=cand))
+    got, launches = _score_launches(
+        lambda: host(pv.pivot_group_index_opts(*args, m, g, c, window=window, out_cand=cand)))
+    edge = max(0, -(-(c - p0) // g))
+    dense, proxies, sb = edge * g, ng - edge, 2 if fmt == "fp8" else 4
+    o = pv.group_opts(m, g, c, window=window)
+    lent = ng * g * pv.pivot_cand_width(o) * sb if mode == "refine" else 0
+    both = (proxies * n_k + dense * min(n_k, p0 + dense)) * sb
+    if min(dense, proxies) < 16:
+        assert launches == 2
+    elif 1.1 * both < lent + max(dense, proxies) * n_k * sb:
+        assert launches == 1, (lent, both)
     if not window:
-        edge = -(-(c - p0) // g)
         groups = sorted({0, edge - 1, edge, edge + 1, ng - 1} | set(range(0, ng, max(1, ng // 7))))
         check_pivot(fmt, x.q[p0:n_k], qs, x.w[p0:n_k], p0, x.k[:n_k], ks, n_k,
                     mode=oracle.REFINE if mode == "refine" else oracle.REUSE, g=g, c=c, topk=topk, dense_below=-1,
                     gpu_idx=got, gpu_cand=None if cand is None else host(cand)[0],
                     groups=[j for j in groups if 0 <= j < ng], label="guardrail")
     a = pv.make_args(*args, torch.empty(n_q, topk, dtype=torch.int32, device="cuda"))
-    o = pv.group_opts(m, g, c, window=window)
     need = pv.pivot_group_workspace_size(a, o)
-    row = ((n_k + 63) // 64 | 1) * 64 * (2 if fmt == "fp8" else 4)
-    rows = min(max(-(-max(0, c - p0) // g) * g, ng - max(0, -(-(c - p0) // g))) - 16, 400)  # a score region of 16 rows and up
-    small = torch.empty(need - max(0, rows) * row, dtype=torch.uint8, device="cuda")
-    one = host(pv.pivot_group_index_opts(*args, m, g, c, window=window, ws=small))
+    row = ((n_k + 63) // 64 | 1) * 64 * sb
+    least = need - max(0, max(dense, proxies) - 16) * row  # a score region of 16 rows
+    small = torch.empty(least, dtype=torch.uint8, device="cuda")
+    one, launches = _score_launches(lambda: host(pv.pivot_group_index_opts(*args, m, g, c, window=window, ws=small)))
     assert np.array_equal(np.sort(one, 1), np.sort(got, 1))
+    if lent < 0.9 * both:
+        assert launches > 1, (lent, both)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("fmt,mode,window", [("bf16", "reuse", 0), ("bf16", "refine", 0), ("bf16", "refine", 8),
+                                             ("fp8", "refine", 8)])
+def test_packed_guardrail_beside_proxies(inputs, fmt, mode, window, paged):
+    """Packed requests of which one lies on both sides of the guardrail, one wholly
+    past it and one wholly below, scored in one launch: contiguous and paged keys,
+    with and without the shared window, every request against the oracle."""
+    specs = [(1100, 0, 1100), (5000, 3000, 517), (2500, 0, 64)]  # (keys, first position, queries)
+    g, c, topk, xs = 4, 256, 128, [inputs[fmt]] * 3
+    (idx, cand, cu), launches = _score_launches(
+        lambda: run_batch(xs, specs, mode, topk, g, c, paged=paged, page=32, window=window, seed=3))
+    assert launches == 1
+    check_batch(xs, specs, mode, topk, idx, cand, cu, g, c, window=window,
+                groups=_groups(specs, g, c, np.random.default_rng(6)))
