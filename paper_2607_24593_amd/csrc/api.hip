@@ -562,8 +562,8 @@ pivot_status dense_part(const pivot_args* a, const Plan& p, void* scores, int64_
 // select launch where topk_both_ok) when both score tiles fit the budget whole:
 // the proxies' workgroups go first and the dense rows' short ones fill the CUs
 // they leave idle.  Apart, each launch ends on its own partial round.  Measured
-// apart and together: 2048 bf16 queries from 0 94.7 -> 74 us a call, five packed
-// requests 766 -> 719, 32768 fp8 queries from 0 1880 -> 1858.  done: whether
+// apart and together: 2048 bf16 queries from 0 92.4 -> 72.7 us a call, five packed
+// requests 774 -> 728, 32768 fp8 queries from 0 1890 -> 1862.  done: whether
 // they were launched.
 pivot_status run_both(const pivot_args* a, const Plan& p, const RowData& rdp, const OutDesc& odp, void* scores,
                       int64_t score_bytes, hipStream_t stream, bool& done) {

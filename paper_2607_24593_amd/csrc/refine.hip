@@ -761,7 +761,7 @@ __device__ __forceinline__ bool member_select16(const uint32_t (&sc)[V / 2], con
   // deviations apart whatever the tails do; the range is cut to 4.5 times that
   // on either side of their middle (beyond every score of a normal row), and
   // the end buckets take what lies outside.  Lanes with an unusable slot don't
-  // count.  256K keys with Pareto amplitudes, 16384 rows: 222 -> 102 us;
+  // count.  256K keys with Pareto amplitudes, 16384 rows: 215 -> 102 us;
   // normal rows unchanged.
   float f_lo = -__builtin_inff(), f_hi = __builtin_inff();
   if constexpr (V >= 16) {
