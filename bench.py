@@ -529,7 +529,7 @@ def recorded_traffic(kernel):
             rec[key] = val
     csrc = os.path.join(ROOT, "paper_2607_24593_amd", "csrc")
     src = b"".join(open(os.path.join(csrc, f), "rb").read()
-                   for f in ("score.hip", "mfma_tile.h", "device_common.h", "api.hip"))
+                   for f in ("score.hip", "segment.h", "mfma_tile.h", "device_common.h", "api.hip"))
     if hashlib.sha256(src).hexdigest() != rec.get("sources_sha256"):
         return None
     return float(rec["read_bytes_per_launch"]) + float(rec["written_bytes_per_launch"])
